@@ -20,7 +20,7 @@ RES_M_MAX = 16
 SYMBOLS = ("resonator_version", "resonator_workspace_bytes", "resonator_mix_fwd",
            "resonator_mix_bwd", "resonator_state_init", "resonator_decode_step",
            "resonator_set_kernel_timer", "resonator_last_error", "resonator_epilogue_fwd",
-           "resonator_epilogue_proj_fwd", "resonator_epilogue_bwd", "resonator_epilogue_workspace_bytes", "resonator_decode_steps",
+           "resonator_epilogue_proj_fwd", "resonator_epilogue_bwd", "resonator_epilogue_workspace_bytes", "resonator_decode_steps", "resonator_decode_steps_tm",
            "resonator_decode_constants", "resonator_decode_step_tab",
            "resonator_params_map", "resonator_params_map_bwd", "resonator_params_init", "resonator_diagnostics",
            "resonator_quadratic_reference", "resonator_quadratic_reference_workspace_bytes",
@@ -124,6 +124,8 @@ def _declare(lib):
     lib.resonator_mix_fwd_noalloc_max_bytes.argtypes = []
     lib.resonator_decode_steps.restype = i32
     lib.resonator_decode_steps.argtypes = [vp, i32, vp, i32, i64, i64, i64, i64, fp, fp, fp, fp, fp, vp]
+    lib.resonator_decode_steps_tm.restype = i32
+    lib.resonator_decode_steps_tm.argtypes = lib.resonator_decode_steps.argtypes
     lib.resonator_decode_constants.restype = i32
     lib.resonator_decode_constants.argtypes = [i64, i64, fp, fp, fp, fp, fp, vp]
     lib.resonator_decode_step_tab.restype = i32

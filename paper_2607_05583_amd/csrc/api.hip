@@ -609,9 +609,10 @@ int resonator_decode_step_tab(const void* x_t, res_dtype_t x_dt, void* y_t, res_
   return e == hipSuccess ? RES_OK : hip_fail(e, "decode launch");
 }
 
-int resonator_decode_steps(const void* x, res_dtype_t x_dt, void* y, res_dtype_t y_dt, int64_t B, int64_t N,
-                           int64_t D, int64_t M, const float* gamma, const float* omega, const float* amp,
-                           const float* phase, float* state, void* stream) {
+// N decode steps on [B][N][D] drives, or [N][B][D] ones (time_major)
+static int decode_steps_impl(const void* x, res_dtype_t x_dt, void* y, res_dtype_t y_dt, int64_t B, int64_t N, int64_t D,
+                             int64_t M, const float* gamma, const float* omega, const float* amp, const float* phase,
+                             float* state, void* stream, bool time_major) {
   int rc = check_sizes(B, N, D, M, false);
   if (rc) return rc;
   if (B > 4 * 65535LL) return fail(RES_ERR_UNSUPPORTED, "B must be <= %lld for this launch (got %lld)",
@@ -630,12 +631,24 @@ int resonator_decode_steps(const void* x, res_dtype_t x_dt, void* y, res_dtype_t
   hipStream_t st = (hipStream_t)stream;
   hipError_t e;
   if (x_dt == RES_F32)
-    e = launch_decode_steps<float, float>(B, N, D, M, x, y, gamma, omega, amp, phase, state, st);
+    e = launch_decode_steps<float, float>(B, N, D, M, x, y, time_major, gamma, omega, amp, phase, state, st);
   else if (y_dt == RES_BF16)
-    e = launch_decode_steps<bf16_t, bf16_t>(B, N, D, M, x, y, gamma, omega, amp, phase, state, st);
+    e = launch_decode_steps<bf16_t, bf16_t>(B, N, D, M, x, y, time_major, gamma, omega, amp, phase, state, st);
   else
-    e = launch_decode_steps<bf16_t, float>(B, N, D, M, x, y, gamma, omega, amp, phase, state, st);
+    e = launch_decode_steps<bf16_t, float>(B, N, D, M, x, y, time_major, gamma, omega, amp, phase, state, st);
   return e == hipSuccess ? RES_OK : hip_fail(e, "decode steps launch");
+}
+
+int resonator_decode_steps(const void* x, res_dtype_t x_dt, void* y, res_dtype_t y_dt, int64_t B, int64_t N,
+                           int64_t D, int64_t M, const float* gamma, const float* omega, const float* amp,
+                           const float* phase, float* state, void* stream) {
+  return decode_steps_impl(x, x_dt, y, y_dt, B, N, D, M, gamma, omega, amp, phase, state, stream, false);
+}
+
+int resonator_decode_steps_tm(const void* x, res_dtype_t x_dt, void* y, res_dtype_t y_dt, int64_t B, int64_t N,
+                              int64_t D, int64_t M, const float* gamma, const float* omega, const float* amp,
+                              const float* phase, float* state, void* stream) {
+  return decode_steps_impl(x, x_dt, y, y_dt, B, N, D, M, gamma, omega, amp, phase, state, stream, true);
 }
 
 // ---------------------------------------------------------------------------

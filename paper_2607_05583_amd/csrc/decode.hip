@@ -14,6 +14,10 @@ namespace res {
 constexpr int DEC_CH = 4;
 constexpr int DEC_ROWS = 64;
 
+// Compiler-level ordering of the LDS accesses of one wave (the LDS executes a
+// wave's accesses in program order).
+__device__ __forceinline__ void wave_order() { asm volatile("" ::: "memory"); }
+
 // One mode's update h <- (hi + lo) h + x and its readout term, with explicit
 // fused multiply-adds so that every decode kernel rounds alike.
 __device__ __forceinline__ float2 mode_step(float2 h, float2 hi, float2 lo, float xv) {
@@ -248,26 +252,139 @@ RES_DECODE_TAB_INST(bf16_t, float)
 
 // ---------------------------------------------------------------------------
 // Several decode steps in one launch, for drives known in advance (a prompt
-// chunk, drafted tokens to verify).  Step n applies the update and readout of
-// decode_kernel with the same constants and in the same order, so N steps here
-// give the same bits as N single steps.  A thread owns one (b, d) and keeps its
-// M modes in registers for all N steps; a wave covers 64 consecutive channels
-// of one batch row, so every step's drive and output rows are coalesced, and
-// the next step's drive is loaded before the current step is computed.
+// chunk, drafted tokens to verify, a captured block of tokens).  Step n applies
+// the update and readout of decode_kernel with the same constants and in the
+// same order, so N steps here give the same bits as N single steps.
+//
+// What bounds it is each mode's chain of dependent steps, so the modes of a
+// (b, d) are spread over R = 8 or 16 lanes, one mode each (B64 D256 M8: 2048
+// waves, two per SIMD; one thread per (b, d) leaves three of four SIMDs idle:
+// 128 steps 52 us, now 17).  The readout needs a
+// step's modes in their order: the lanes take R steps, leave every step's states
+// in LDS, and lane r then reads out step r with all its modes, so the readout
+// is spread over the lanes by step.  Lane r also loads step r's drive, one
+// batch of R steps ahead.  All exchange stays inside a wave (no barrier in the
+// step loop).
+//
+// A block is CH channels x DMS_ROWS batch rows (one wave per row).  The
+// DMS_XCD blocks of neighbouring channels that share the 128-byte lines of a
+// row's drives and outputs are 8 apart in the grid, which the dispatcher places
+// on one XCD (work-groups go round-robin over the 8 XCDs).
 // ---------------------------------------------------------------------------
-constexpr int DMS_CH = 64;
-constexpr int DMS_ROWS = 4;
+constexpr int DMS_ROWS = 4;  // waves of a block
+constexpr int DMS_XCD = 8;
 
-template <typename TX, typename TY, int MM>
-__global__ __launch_bounds__(DMS_CH* DMS_ROWS) void decode_steps_kernel(
-    const TX* __restrict__ x, TY* __restrict__ y, int B, int64_t N, int D, int M,
+template <typename TX, typename TY, int R>
+__global__ __launch_bounds__(64 * DMS_ROWS) void decode_steps_kernel(
+    const TX* __restrict__ x, TY* __restrict__ y, int B, int64_t N, int D, int M, int64_t sn, int64_t sb,
     const float* __restrict__ gamma, const float* __restrict__ omega, const float* __restrict__ amp,
     const float* __restrict__ phase, float* __restrict__ state) {
-  __shared__ float2 lhi[DMS_CH][MM], llo[DMS_CH][MM], cs[DMS_CH][MM];
+  constexpr int CH = 64 / R;         // channels of a block
+  constexpr int HROW = R + 2;        // float2 per step row of the states (16 bytes of bank offset)
+  constexpr int HGRP = R * HROW + 8; // float2 per (b, d)
+  __shared__ float2 lhi[64], llo[64], cs[64];
+  __shared__ __align__(16) float xs[DMS_ROWS * CH][R];
+  __shared__ __align__(16) float2 hs[DMS_ROWS * CH * HGRP];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int m = lane % R, cl = lane / R;
+  // block -> (row block, channel block): member k of a group of DMS_XCD channel
+  // blocks, groups over channels then rows
+  const unsigned bid = blockIdx.x;
+  const int64_t grp = (int64_t)(bid / (8 * DMS_XCD)) * 8 + (bid & 7);
+  const int ngd = (D + CH * DMS_XCD - 1) / (CH * DMS_XCD);
+  const int d0 = ((int)(grp % ngd) * DMS_XCD + (int)((bid >> 3) % DMS_XCD)) * CH;
+  const int64_t b0 = grp / ngd * DMS_ROWS;
+  if (d0 >= D || b0 >= B) return;  // the whole block
+  const int64_t b = b0 + wave;
+  const int d = d0 + cl;
+  const bool valid = b < B && d < D;
+  const int64_t bc = b < B ? b : B - 1;
+  const int dc = d < D ? d : D - 1;
+  // the state and the first R drives load while the constants are evaluated
+  float2* st = reinterpret_cast<float2*>(state) + ((size_t)bc * D + dc) * M;
+  float2 h = make_float2(0.f, 0.f);
+  if (m < M) h = st[m];
+  const int64_t xo = bc * sb + dc;
+  TX xn = x[(m < N ? (int64_t)m : N - 1) * sn + xo];
+  if (threadIdx.x < 64) {
+    float2 hi = make_float2(0.f, 0.f), lo = hi, c = hi;
+    if (d < D && m < M) {
+      const int i = d * M + m;
+      decode_consts(gamma[i], omega[i], amp[i], phase[i], hi, lo, c);
+    }
+    lhi[lane] = hi;
+    llo[lane] = lo;
+    cs[lane] = c;
+  }
+  __syncthreads();
+  const float2 hi = lhi[lane], lo = llo[lane];
+  float2 c[R];
+#pragma unroll
+  for (int k = 0; k < R; ++k) c[k] = cs[cl * R + k];
+  float* xg = xs[wave * CH + cl];
+  float2* hg = hs + (size_t)(wave * CH + cl) * HGRP;
+  for (int64_t n0 = 0; n0 < N; n0 += R) {
+    xg[m] = to_f32(xn);
+    {  // past the last step the index is clamped to it and the value is not used
+      const int64_t nn = n0 + R + m;
+      xn = x[(nn < N ? nn : N - 1) * sn + xo];
+    }
+    wave_order();
+    const int nr = N - n0 < R ? (int)(N - n0) : R;
+    float xv[R];
+#pragma unroll
+    for (int j = 0; j < R; j += 4) {
+      const float4 v = *reinterpret_cast<const float4*>(xg + j);
+      xv[j] = v.x;
+      xv[j + 1] = v.y;
+      xv[j + 2] = v.z;
+      xv[j + 3] = v.w;
+    }
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+      if (j < nr) {
+        h = mode_step(h, hi, lo, xv[j]);
+        hg[j * HROW + m] = h;
+      }
+    }
+    wave_order();
+    float yv = 0.f;
+    const float4* hr = reinterpret_cast<const float4*>(hg + m * HROW);
+#pragma unroll
+    for (int k = 0; k < R; k += 2) {
+      const float4 v = hr[k / 2];
+      if (k < M) yv = mode_readout(c[k], make_float2(v.x, v.y), yv);
+      if (k + 1 < M) yv = mode_readout(c[k + 1], make_float2(v.z, v.w), yv);
+    }
+    if (valid && m < nr) y[(n0 + m) * sn + xo] = from_f32<TY>(yv);
+    wave_order();
+  }
+  if (valid && m < M) st[m] = h;
+}
+
+// The same steps for many (b, d): a thread owns one (b, d) and keeps its M modes
+// in registers for all N steps; a wave covers 64 consecutive channels of one
+// batch row, so every step's drive and output rows are coalesced, and the next
+// step's drive is loaded before the current step is computed.  With enough
+// waves to fill the SIMDs it needs no exchange and is the faster one.
+constexpr int DMW_CH = 64;
+constexpr int DMW_ROWS = 4;
+// (b, d) pairs above which one thread per pair is faster (128 steps, M = 8: at
+// 16384 pairs 52 us against 17 with a lane per mode, at 65536 55 against 38, at
+// 131072 58 against 65, at 262144 92 against 125; M = 2: 35 against 36 at 65536,
+// 37 against 46 at 98304; M = 16: 99 against 68 and 105 against 132)
+constexpr int64_t DMW_MAX_PAIRS = 1 << 16;
+
+template <typename TX, typename TY, int MM>
+__global__ __launch_bounds__(DMW_CH* DMW_ROWS) void decode_steps_wide_kernel(
+    const TX* __restrict__ x, TY* __restrict__ y, int B, int64_t N, int D, int M, int64_t sn, int64_t sb,
+    const float* __restrict__ gamma, const float* __restrict__ omega, const float* __restrict__ amp,
+    const float* __restrict__ phase, float* __restrict__ state) {
+  __shared__ float2 lhi[DMW_CH][MM], llo[DMW_CH][MM], cs[DMW_CH][MM];
   const int tid = threadIdx.x;
-  const int d0 = blockIdx.x * DMS_CH;
-  const int b0 = blockIdx.y * DMS_ROWS;
-  for (int t = tid; t < DMS_CH * M; t += blockDim.x) {
+  const int d0 = blockIdx.x * DMW_CH;
+  const int b0 = blockIdx.y * DMW_ROWS;
+  for (int t = tid; t < DMW_CH * M; t += blockDim.x) {
     const int dl = t / M, m = t % M, d = d0 + dl;
     float2 hi = make_float2(0.f, 0.f), lo = hi, c = hi;
     if (d < D) decode_consts(gamma[d * M + m], omega[d * M + m], amp[d * M + m], phase[d * M + m], hi, lo, c);
@@ -276,8 +393,8 @@ __global__ __launch_bounds__(DMS_CH* DMS_ROWS) void decode_steps_kernel(
     cs[dl][m] = c;
   }
   __syncthreads();
-  const int dl = tid % DMS_CH;
-  const int b = b0 + tid / DMS_CH;
+  const int dl = tid % DMW_CH;
+  const int b = b0 + tid / DMW_CH;
   const int d = d0 + dl;
   if (b >= B || d >= D) return;  // no barrier follows
   float2 h[MM], hi[MM], lo[MM], c[MM];
@@ -291,21 +408,21 @@ __global__ __launch_bounds__(DMS_CH* DMS_ROWS) void decode_steps_kernel(
       c[m] = cs[dl][m];
     }
   }
-  const TX* xr = x + (size_t)b * N * D + d;
-  TY* yr = y + (size_t)b * N * D + d;
+  const TX* xr = x + (size_t)b * sb + d;
+  TY* yr = y + (size_t)b * sb + d;
   // Drives of the next DPF steps are loaded while the current DPF are computed.
   // Past the last step the index is clamped to it (the value is not used), so
   // the loads are unconditional and none waits behind a branch.
   constexpr int DPF = 8;
   TX xb[DPF];
 #pragma unroll
-  for (int j = 0; j < DPF; ++j) xb[j] = xr[(j < N ? (int64_t)j : N - 1) * D];
+  for (int j = 0; j < DPF; ++j) xb[j] = xr[(j < N ? (int64_t)j : N - 1) * sn];
   for (int64_t n0 = 0; n0 < N; n0 += DPF) {
     TX xn[DPF];
 #pragma unroll
     for (int j = 0; j < DPF; ++j) {
       const int64_t nn = n0 + DPF + j;
-      xn[j] = xr[(nn < N ? nn : N - 1) * D];
+      xn[j] = xr[(nn < N ? nn : N - 1) * sn];
     }
 #pragma unroll
     for (int j = 0; j < DPF; ++j) {
@@ -318,7 +435,7 @@ __global__ __launch_bounds__(DMS_CH* DMS_ROWS) void decode_steps_kernel(
             yv = mode_readout(c[m], h[m], yv);
           }
         }
-        yr[(n0 + j) * D] = from_f32<TY>(yv);
+        yr[(n0 + j) * sn] = from_f32<TY>(yv);
       }
     }
 #pragma unroll
@@ -330,25 +447,39 @@ __global__ __launch_bounds__(DMS_CH* DMS_ROWS) void decode_steps_kernel(
 }
 
 template <typename TX, typename TY>
-hipError_t launch_decode_steps(int64_t B, int64_t N, int64_t D, int64_t M, const void* x, void* y,
+hipError_t launch_decode_steps(int64_t B, int64_t N, int64_t D, int64_t M, const void* x, void* y, bool time_major,
                                const float* gamma, const float* omega, const float* amp,
                                const float* phase, float* state, hipStream_t st) {
-  const dim3 grid((unsigned)((D + DMS_CH - 1) / DMS_CH), (unsigned)((B + DMS_ROWS - 1) / DMS_ROWS));
-  if (M <= 8)
-    hipLaunchKernelGGL((decode_steps_kernel<TX, TY, 8>), grid, dim3(DMS_CH * DMS_ROWS), 0, st,
-                       reinterpret_cast<const TX*>(x), reinterpret_cast<TY*>(y), (int)B, N, (int)D,
-                       (int)M, gamma, omega, amp, phase, state);
+  const int64_t sn = time_major ? B * D : D, sb = time_major ? D : N * D;
+  if (B * D > DMW_MAX_PAIRS) {
+    const dim3 wgrid((unsigned)((D + DMW_CH - 1) / DMW_CH), (unsigned)((B + DMW_ROWS - 1) / DMW_ROWS));
+    if (M <= 8)
+      hipLaunchKernelGGL((decode_steps_wide_kernel<TX, TY, 8>), wgrid, dim3(DMW_CH * DMW_ROWS), 0, st,
+                         reinterpret_cast<const TX*>(x), reinterpret_cast<TY*>(y), (int)B, N, (int)D, (int)M, sn, sb,
+                         gamma, omega, amp, phase, state);
+    else
+      hipLaunchKernelGGL((decode_steps_wide_kernel<TX, TY, RES_M_MAX_DEV>), wgrid, dim3(DMW_CH * DMW_ROWS), 0, st,
+                         reinterpret_cast<const TX*>(x), reinterpret_cast<TY*>(y), (int)B, N, (int)D, (int)M, sn, sb,
+                         gamma, omega, amp, phase, state);
+    return hipGetLastError();
+  }
+  const int R = M <= 8 ? 8 : 16;
+  const int64_t gch = 64 / R * DMS_XCD;  // channels of a group of blocks
+  const int64_t groups = (D + gch - 1) / gch * ((B + DMS_ROWS - 1) / DMS_ROWS);
+  const dim3 grid((unsigned)((groups + 7) / 8 * 8 * DMS_XCD)), block(64 * DMS_ROWS);
+  if (R == 8)
+    hipLaunchKernelGGL((decode_steps_kernel<TX, TY, 8>), grid, block, 0, st, reinterpret_cast<const TX*>(x),
+                       reinterpret_cast<TY*>(y), (int)B, N, (int)D, (int)M, sn, sb, gamma, omega, amp, phase, state);
   else
-    hipLaunchKernelGGL((decode_steps_kernel<TX, TY, RES_M_MAX_DEV>), grid, dim3(DMS_CH * DMS_ROWS), 0, st,
-                       reinterpret_cast<const TX*>(x), reinterpret_cast<TY*>(y), (int)B, N, (int)D,
-                       (int)M, gamma, omega, amp, phase, state);
+    hipLaunchKernelGGL((decode_steps_kernel<TX, TY, 16>), grid, block, 0, st, reinterpret_cast<const TX*>(x),
+                       reinterpret_cast<TY*>(y), (int)B, N, (int)D, (int)M, sn, sb, gamma, omega, amp, phase, state);
   return hipGetLastError();
 }
 
 #define RES_DECODE_STEPS_INST(TX, TY)                                                                   \
   template hipError_t launch_decode_steps<TX, TY>(int64_t, int64_t, int64_t, int64_t, const void*, void*, \
-                                                  const float*, const float*, const float*, const float*, \
-                                                  float*, hipStream_t);
+                                                  bool, const float*, const float*, const float*,       \
+                                                  const float*, float*, hipStream_t);
 RES_DECODE_STEPS_INST(float, float)
 RES_DECODE_STEPS_INST(bf16_t, bf16_t)
 RES_DECODE_STEPS_INST(bf16_t, float)

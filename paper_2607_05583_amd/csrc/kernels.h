@@ -202,7 +202,7 @@ template <typename TX, typename TY>
 hipError_t launch_decode_tab(int64_t B, int64_t D, int64_t M, const void* x, void* y, const float* tab,
                              float* state, hipStream_t st);
 template <typename TX, typename TY>
-hipError_t launch_decode_steps(int64_t B, int64_t N, int64_t D, int64_t M, const void* x, void* y,
+hipError_t launch_decode_steps(int64_t B, int64_t N, int64_t D, int64_t M, const void* x, void* y, bool time_major,
                                const float* gamma, const float* omega, const float* amp,
                                const float* phase, float* state, hipStream_t st);
 

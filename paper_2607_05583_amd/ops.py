@@ -245,19 +245,17 @@ def resonator_decode_steps(x, gamma, omega, amp, phase, state, out_dtype=None, o
 
 
 class DecodeGraph:
-    """K decode steps (Sec. 3.3) captured once as a HIP graph and replayed: one
-    token's step is a single short launch, so a replay issues the K launches of a
-    block of tokens without K host round trips.
+    """K decode steps (Sec. 3.3) of a block of tokens captured once as a HIP graph
+    and replayed.
 
     Static buffers: ``x`` [K, B, D] holds the drives of the next K tokens (copy
     them in, or pass them to ``replay``), ``y`` [K, B, D] receives the outputs;
     ``state`` [B, D, M, 2] is updated in place by every replay.  The parameters
     and the state are captured by address: update them in place, never rebind
-    them.  A replay first evaluates the decode constants from the parameters into
-    a table (one launch), then runs the K steps from the table
-    (resonator_decode_step_tab, bitwise resonator_decode_step).  The capture
-    records these kernels only (no allocation, no memset), and nothing runs until
-    the first replay."""
+    them.  A block's drives are all in ``x`` when a replay starts, so the capture
+    records one launch that runs the K steps (resonator_decode_steps_tm, bitwise K
+    single steps; constants evaluated from the parameters by that launch), no
+    allocation and no memset, and nothing runs until the first replay."""
 
     def __init__(self, gamma, omega, amp, phase, state, steps: int, x_dtype=torch.bfloat16, out_dtype=None):
         _dev(state, "state")
@@ -274,16 +272,15 @@ class DecodeGraph:
         self.state = state
         self.x = torch.zeros((steps, B, D), dtype=x_dtype, device=dev)
         self.y = torch.empty((steps, B, D), dtype=out_dtype, device=dev)
-        self.tab = torch.empty((D, M, 6), dtype=torch.float32, device=dev)
         _lib.lib()  # loaded before the capture
         self.graph = torch.cuda.CUDAGraph()
         cur = torch.cuda.current_stream(dev)
         cap = torch.cuda.Stream(dev)
         cap.wait_stream(cur)
         with torch.cuda.stream(cap), torch.cuda.graph(self.graph, stream=cap):
-            resonator_decode_constants(*self.params, out=self.tab)
-            for k in range(steps):
-                resonator_decode_step_tab(self.x[k], self.tab, state, out=self.y[k])
+            check(_lib.lib().resonator_decode_steps_tm(
+                _ptr(self.x), _code(self.x), _ptr(self.y), _code(self.y), B, steps, D, M, *map(_ptr, self.params),
+                _ptr(state), _stream(dev)))
         cur.wait_stream(cap)
 
     def replay(self, x=None):

@@ -225,6 +225,25 @@ def test_decode_graph_replays_match_eager_steps(B, D, M, K, act):
         _ = (x.float() * 2).sum().item()  # unrelated eager work between the replays
 
 
+@pytest.mark.parametrize("B,D,M,N,act", [(1, 1, 1, 8, "f32"), (5, 65, 8, 7, "bf16"), (5, 63, 9, 17, "bf16"),
+                                         (256, 256, 2, 9, "f32"), (257, 256, 3, 9, "bf16"), (1024, 65, 9, 3, "f32")])
+def test_decode_steps_kernel_choice(B, D, M, N, act):
+    """Both kernels of several steps (a lane per mode up to 65536 (b, d) pairs, a
+    thread per pair above), on batch-major and time-major drives and at the
+    remainders of the lanes' step batches: bitwise N single steps."""
+    say(f"decode steps kernels B={B} D={D} M={M} N={N} {act}")
+    prob = W.random_problem(171 + B, B, N, D, M, act=act, gamma_range=(1e-4, 1.0), gamma_log=True, with_h0=True)
+    x, pr = dev_act(prob["x"], act), params_dev(prob)
+    st0 = torch.from_numpy(prob["h0"]).cuda()
+    st1, st2, st3 = st0.clone(), st0.clone(), st0.clone()
+    ye = torch.stack([ops.resonator_decode_step(x[:, t].contiguous(), *pr, st1) for t in range(N)], 1)
+    yn = ops.resonator_decode_steps(x, *pr, st2)
+    yg = ops.DecodeGraph(*pr, st3, N, x_dtype=x.dtype).replay(x.transpose(0, 1).contiguous())
+    torch.cuda.synchronize()
+    assert torch.equal(yn, ye) and torch.equal(st2, st1)
+    assert torch.equal(yg, ye.transpose(0, 1)) and torch.equal(st3, st1)
+
+
 def _oracle_rows(args):
     """Oracle recurrence over one group of batch rows (a worker thread's share)."""
     x, h0, prm = args
