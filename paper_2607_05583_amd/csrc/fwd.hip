@@ -667,91 +667,89 @@ constexpr uint32_t SPIN_LIMIT = 1u << 18;
 // Polls of the wait for the other work-groups of a chain to arrive (some tens of
 // microseconds at most); past it the chain takes its tiles by ticket.
 constexpr uint32_t ARRIVE_WAIT = 64;
-#ifndef RES_FOLD_WORDS
-#define RES_FOLD_WORDS 16
-#endif
+// Sixteen zero bytes: the source of the pieces of a tile that lie outside the tensor.
+__device__ const uint4 zero_piece = {0u, 0u, 0u, 0u};
 
-// Direct-to-LDS load of row group g (8 rows of 128 bytes, one 16-byte load
-// per lane) of a full tile by the calling wave.
-template <typename TX>
-__device__ __forceinline__ void dma_group(char* xt, const TX* x, int64_t b, int64_t t0, int d0, int64_t L,
-                                          int D, int lane, int g) {
-  constexpr int XE = (int)sizeof(TX);
-  const int64_t rowb = (int64_t)D * XE;
-  const char* src = reinterpret_cast<const char*>(x) + ((b * L + t0) * D + d0) * XE + (int64_t)(8 * g) * rowb;
-  // the lane's offset, recomputed here rather than kept live across the loops
-  int ln = lane;
-  asm volatile("" : "+v"(ln));
-  const uint32_t loff = (uint32_t)((ln >> 3) * rowb) + (ln & 7) * 16;
-  lds_dma16(src, loff, xt + g * XLay<XE>::GRP);
-}
-
-// Row groups g0, g0 + step, ... (n of them) of a full output tile from its LDS
-// buffer by the calling wave: all the LDS reads first (a 16-byte row piece per
-// lane, read as two 8-byte halves), then the 16-byte row stores.
-template <typename TY, int N>
-__device__ __forceinline__ void store_groups(TY* y, const char* xt, int64_t b, int64_t t0, int d0, int64_t L,
-                                             int D, int lane, int g0, int step) {
-  constexpr int YE = (int)sizeof(TY);
-  const int64_t rowb = (int64_t)D * YE;
-  char* dst = reinterpret_cast<char*>(y) + ((b * L + t0) * D + d0) * YE;
-  int ln = lane;
-  asm volatile("" : "+v"(ln));
-  u32x4 v[N];
-#pragma unroll
-  for (int i = 0; i < N; ++i) {
-    const uint2* s = reinterpret_cast<const uint2*>(xt + (g0 + step * i) * XLay<YE>::GRP + ln * 16);
-    const uint2 u = s[0], w = s[1];
-    v[i] = u32x4{u.x, u.y, w.x, w.y};
-  }
-  const uint32_t loff = (uint32_t)((ln >> 3) * rowb) + (ln & 7) * 16;
-#pragma unroll
-  for (int i = 0; i < N; ++i) st_row16(dst + (int64_t)(8 * (g0 + step * i)) * rowb, loff, v[i]);
-}
-
-// Element copy of a tile that is not full (NT threads); zeros outside the tensor.
+// Element copy of a tile whose rows are not 16-byte pieces (NT threads, eight
+// loads issued together); zeros outside the tensor.
 template <typename TX, int NT>
 __device__ __forceinline__ void copy_tile(char* xt, const TX* x, int64_t b, int64_t t0, int d0, int64_t L,
                                           int D, int tid) {
-  constexpr int DW = tile_channels<TX>(), XE = (int)sizeof(TX);
-  for (int idx = tid; idx < TILE_T * DW; idx += NT) {
-    const int t = idx / DW, c = idx % DW;
-    TX v = from_f32<TX>(0.f);
-    if (t0 + t < L && d0 + c < D) v = x[(b * L + t0 + t) * (int64_t)D + d0 + c];
-    *reinterpret_cast<TX*>(xt + XLay<XE>::off(t) + c * XE) = v;
+  constexpr int DW = tile_channels<TX>(), XE = (int)sizeof(TX), NB = 8;
+  static_assert(TILE_T * DW % (NB * NT) == 0, "whole batches");
+  asm volatile("" : "+v"(tid));  // addresses formed here rather than kept live across the caller's loops
+  const TX* base = x + (b * L + t0) * D + d0;
+  for (int i0 = tid; i0 < TILE_T * DW; i0 += NB * NT) {
+    TX v[NB];
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+      const int t = (i0 + i * NT) / DW, c = (i0 + i * NT) % DW;
+      v[i] = from_f32<TX>(0.f);
+      if (t0 + t < L && d0 + c < D) v[i] = base[(int64_t)t * D + c];
+    }
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+      const int t = (i0 + i * NT) / DW, c = (i0 + i * NT) % DW;
+      *reinterpret_cast<TX*>(xt + XTile<XE>::off(t, c * XE)) = v[i];
+    }
   }
 }
 
-// Output tile that is not full, from its LDS buffer (NT threads): guarded
-// element stores.
+// Output tile whose rows are not 16-byte pieces, from its LDS buffer (NT
+// threads): guarded element stores.
 template <typename TY, int NT>
 __device__ __forceinline__ void store_tile_part(TY* y, const char* xt, int64_t b, int64_t t0, int d0, int64_t L,
                                                 int D, int tid) {
   constexpr int DW = tile_channels<TY>(), YE = (int)sizeof(TY);
+  asm volatile("" : "+v"(tid));
+#pragma unroll 4
   for (int idx = tid; idx < TILE_T * DW; idx += NT) {
     const int t = idx / DW, c = idx % DW;
     if (t0 + t < L && d0 + c < D)
-      y[(b * L + t0 + t) * (int64_t)D + d0 + c] = *reinterpret_cast<const TY*>(xt + XLay<YE>::off(t) + c * YE);
+      y[(b * L + t0 + t) * (int64_t)D + d0 + c] = *reinterpret_cast<const TY*>(xt + XTile<YE>::off(t, c * YE));
+  }
+}
+
+// Outputs of 4 channels (MFMA D layout, lane (n, q) holds rows 16n + 4q + r) to
+// the byte address p of row 16n + 4q of an XTile.
+template <typename TY>
+__device__ __forceinline__ void put_rows4(char* p, const f4 (&acc)[4]) {
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    if constexpr (sizeof(TY) == 2) {
+      typedef __bf16 bf4 __attribute__((ext_vector_type(4)));
+      const bf4 v = {(__bf16)acc[0][r], (__bf16)acc[1][r], (__bf16)acc[2][r], (__bf16)acc[3][r]};
+      *reinterpret_cast<bf4*>(p + r * XROW) = v;
+    } else {
+      *reinterpret_cast<f4*>(p + r * XROW) = f4{acc[0][r], acc[1][r], acc[2][r], acc[3][r]};
+    }
   }
 }
 
 template <typename TX>
 struct StreamGeo {
   static constexpr int DW = tile_channels<TX>();   // channels per tile: 64 (bf16) | 32 (float)
-  static constexpr int NW = 8;                     // waves (two per SIMD: 256 registers each)
-  static constexpr int NG = DW / (4 * NW);         // groups of 4 channels per wave: 2 | 1
+  // Waves, each with one group of 4 channels: 16 (bf16, four per SIMD, 128
+  // registers each) | 8 (float).  More waves, not more channels per wave: a tile
+  // step is a chain of LDS and matrix latencies that the other waves of the SIMD
+  // fill (bf16 with 8 waves of 8 channels: 61 against 53 thousand cycles for the
+  // output pass at B4 L32K).
+  static constexpr int NW = DW / 4;
   static constexpr int NT = 64 * NW;
-  static constexpr int NQ = 0;                     // first load wave
-  static constexpr int LW = NW;                    // load waves (every wave loads and stores rows)
-  static constexpr int GPL = (TILE_T / 8) / LW;    // row groups per load wave and tile
+  static constexpr int GPL = (TILE_T / 8) / NW;    // row groups per wave and tile
   static constexpr int NBUF = 4;                   // tile buffers
-  static constexpr int HKS = 16 * 16 + 8;          // floats per channel in the H transposition (8 of bank offset)
-  static constexpr int XB = XLay<(int)sizeof(TX)>::BYTES;
-  static constexpr int HB = NW * 4 * HKS * 4;      // every wave's 4 channels of one group
+  // The H transposition: a channel's 16 chunks x 16 components, 4 / HP channels
+  // of every wave at a time (all of it would not fit beside the tiles with 16
+  // waves).  Channel c starts at float c HKS + 8 (c & 1), so that the 32 lanes of
+  // a write (two channels) meet 32 banks.
+  static constexpr int HKS = 16 * 16 + 8;
+  static constexpr int HP = NW / 8;
+  static constexpr int HW = (4 / HP) * HKS;        // floats per wave
+  static constexpr int XB = XTile<(int)sizeof(TX)>::BYTES;
+  static constexpr int HB = NW * HW * 4;
   static constexpr int BUFB = XB > HB ? XB : HB;   // bytes per buffer (tile, or H transposition)
-  static_assert(GPL * LW == TILE_T / 8, "the load waves cover a tile");
-  static_assert(NQ + LW <= NW, "control and load waves are distinct");
-  static_assert(NG * 4 * NW == DW, "the waves cover the tile's channels");
+  static_assert(GPL * NW * 8 == TILE_T, "the waves cover a tile");
+  static_assert(BUFB % 16 == 0 && HW % 16 == 0, "16-byte buffers, 64-byte H regions");
 };
 
 // LDS stage of a work-group's tables, per channel k of the block and mode m:
@@ -953,87 +951,112 @@ __device__ __forceinline__ void chunk_states(const typename FPath<TX>::XOp (&xv)
 // the tag of the call that wrote it (high half), so that a reader checks the
 // data itself and a writer needs no ordering between data and a flag.  The
 // stores and loads are device-coherent (work-groups of a chain run on any XCD).
-template <int NG>
-__device__ __forceinline__ void put_state(uint64_t* p, const float (&v)[NG], uint32_t tag) {
-#pragma unroll
-  for (int g = 0; g < NG; ++g)
-    __hip_atomic_store(p + g, (uint64_t)__float_as_uint(v[g]) | ((uint64_t)tag << 32), __ATOMIC_RELAXED,
-                       __HIP_MEMORY_SCOPE_AGENT);
+__device__ __forceinline__ void put_state(uint64_t* p, float v, uint32_t tag) {
+  __hip_atomic_store(p, (uint64_t)__float_as_uint(v) | ((uint64_t)tag << 32), __ATOMIC_RELAXED,
+                     __HIP_MEMORY_SCOPE_AGENT);
 }
-// false while any word still carries another tag
-template <int NG>
-__device__ __forceinline__ bool get_state(const uint64_t* p, uint32_t tag, float (&v)[NG]) {
-  bool ok = true;
-#pragma unroll
-  for (int g = 0; g < NG; ++g) {
-    const uint64_t w = __hip_atomic_load(p + g, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    v[g] = __uint_as_float((uint32_t)w);
-    ok = ok && (uint32_t)(w >> 32) == tag;
-  }
-  return ok;
+// false while the word still carries another tag
+__device__ __forceinline__ bool get_state(const uint64_t* p, uint32_t tag, float& v) {
+  const uint64_t w = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  v = __uint_as_float((uint32_t)w);
+  return (uint32_t)(w >> 32) == tag;
 }
 
-template <typename TX, typename TY>
+template <typename TX, typename TY, bool DMA>
 __global__ __launch_bounds__(StreamGeo<TX>::NT, 1) void fwd_stream_kernel(StreamArgs a) {
   typedef StreamGeo<TX> G;
   typedef FPath<TX> PT;
   typedef TabStage<TX> TS;
-  constexpr int DW = G::DW, NW = G::NW, NG = G::NG, NT = G::NT, NQ = G::NQ, LW = G::LW, GPL = G::GPL;
-  constexpr int NBUF = G::NBUF, XE = (int)sizeof(TX), HKS = G::HKS;
+  constexpr int DW = G::DW, NW = G::NW, NT = G::NT, GPL = G::GPL;
+  constexpr int NBUF = G::NBUF, XE = (int)sizeof(TX), HKS = G::HKS, HP = G::HP;
   static_assert(TS::BYTES <= (NBUF - 1) * G::BUFB, "the table stage fits in buffers 1 .. NBUF-1");
   static_assert(NBUF == 4, "buffer rotation assumes four buffers");
   // bf16 drive with float32 output: y leaves straight from the MFMA registers
   constexpr bool SEPY = !__is_same(TX, TY);
-  // published states loaded at a time by the look-back (a register budget of 2 RES_FOLD_WORDS)
-  constexpr int FB = RES_FOLD_WORDS / NG;
-  __shared__ __align__(16) char xb[NBUF][G::BUFB];
+  // published states loaded at a time by the look-back
+  constexpr int FB = 8;
+  __shared__ __align__(64) char xb[NBUF][G::BUFB];
   __shared__ KConst s_kc[DW * 8];
   __shared__ uint32_t s_u[4];
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int ln = lane & 15, lq = lane >> 4;  // MFMA lane (i, q); scan lane (component ln, channel lq)
-  const int cb = wave * 4 * NG;              // this wave's first channel; group g: cb + 4 g .. cb + 4 g + 3
-  const bool is_ld = wave >= NQ && wave < NQ + LW;
+  const int cb = 4 * wave;                   // this wave's first channel
   const int chain = (int)(blockIdx.x % (unsigned)a.nchains);
   const int64_t b = chain / a.NB;
   const int blk = chain % a.NB;
   const int d0 = blk * DW;
-  const int64_t P = a.P;
+  const int P = (int)a.P;
   const uint32_t G_ = gridDim.x / (uint32_t)a.nchains;  // work-groups (segments) of each chain
-  // (channel, mode) of scan lane (component ln, channel lq) of group g
-  auto kmode = [&](int g) { return (cb + 4 * g + lq) * 8 + (ln >> 1); };
+  const int kmode = (cb + lq) * 8 + (ln >> 1);  // (channel, mode) of scan lane (component ln, channel lq)
   // segment j: tiles [j Sf + min(j, Sr), ... + Sf + (j < Sr))
-  const int64_t Sf = P / G_, Sr = P % G_;
-  auto seg_start = [&](int64_t j) { return j * Sf + (j < Sr ? j : Sr); };
+  const int Sf = P / (int)G_, Sr = P % (int)G_;
+  auto seg_start = [&](int j) { return j * Sf + (j < Sr ? j : Sr); };
   uint32_t* cw = a.chainw + 4 * (size_t)chain;  // [0] next ticket, [1] arrived, [2] order, [3] finished
   const uint32_t ep = ld_flag(a.hdr + 1);
   const uint32_t TAG = ep + 1u;
   const int nstar = (a.last_len - 1) / CHUNK, jstar = (a.last_len - 1) % CHUNK;
   const f4 zero = {0.f, 0.f, 0.f, 0.f};
-  const bool full_block = a.fast_io && d0 + DW <= a.D;
-  auto tile_full = [&](int64_t p) { return full_block && (p + 1) * TILE_T <= a.L; };
-  auto load_tile = [&](int u, int64_t p) {  // by the load waves, a full tile
-#pragma unroll
-    for (int i = 0; i < GPL; ++i)
-      dma_group<TX>(xb[u], reinterpret_cast<const TX*>(a.x), b, p * TILE_T, d0, a.L, a.D, lane,
-                    (wave - NQ) + LW * i);
+  // With 16-byte pieces (DMA) every wave loads and stores its own row groups
+  // wave + NW i of a tile; tiles below Pfull are whole, the others take the
+  // pieces outside the tensor from zero_piece and do not store them.
+  const int Pfull = DMA && d0 + DW <= a.D ? (int)(a.L / TILE_T) : 0;
+  const int64_t rowb = (int64_t)a.D * XE;
+  const int64_t row0 = (b * a.L + 8 * wave) * rowb + (int64_t)d0 * XE;  // the wave's first row in the tensor
+  const char* xw = reinterpret_cast<const char*>(a.x) + row0;
+  char* yw = reinterpret_cast<char*>(a.y) + row0;                       // (not used when y has another type)
+  // the lane's row and piece of a group of 8 rows (slot lane & 7; h: the chunk's swizzle)
+  auto lane_off = [&](int i) {
+    int l = lane;
+    asm volatile("" : "+v"(l));  // recomputed rather than kept live across the loops
+    const int hsw = ((wave + NW * i) >> 1) & 7;
+    return (uint32_t)((l >> 3) * (int)rowb) + (uint32_t)(((l & 7) ^ hsw) << 4);
   };
-  auto store_tile = [&](int u, int64_t p) {  // rows of output tile p from buffer u
-    if (tile_full(p)) {
-      if (is_ld) {
-        constexpr int SB = GPL < 4 ? GPL : 4;  // row groups per batch of LDS reads
+  auto piece_in = [&](int p, int i) {  // whether the lane's piece of group i of tile p is in the tensor
+    const int hsw = ((wave + NW * i) >> 1) & 7;
+    return (int64_t)p * TILE_T + 8 * (wave + NW * i) + (lane >> 3) < a.L &&
+           d0 + ((lane & 7) ^ hsw) * (16 / XE) < a.D;
+  };
+  auto load_tile = [&](int u, int p) {
+    const char* src = xw + (int64_t)p * (TILE_T * rowb);
+    if (p < Pfull) {
 #pragma unroll
-        for (int i = 0; i < GPL; i += SB)
-          store_groups<TY, SB>(reinterpret_cast<TY*>(a.y), xb[u], b, p * TILE_T, d0, a.L, a.D, lane,
-                               (wave - NQ) + LW * i, LW);
-      }
+      for (int i = 0; i < GPL; ++i)
+        lds_dma16(src + (int64_t)(8 * NW * i) * rowb, lane_off(i), xb[u] + XTile<XE>::group(wave + NW * i));
     } else {
-      store_tile_part<TY, NT>(reinterpret_cast<TY*>(a.y), xb[u], b, p * TILE_T, d0, a.L, a.D, tid);
+#pragma unroll
+      for (int i = 0; i < GPL; ++i) {
+        const char* q = src + (int64_t)(8 * NW * i) * rowb + lane_off(i);
+        lds_dma16_lane(piece_in(p, i) ? q : reinterpret_cast<const char*>(&zero_piece),
+                       xb[u] + XTile<XE>::group(wave + NW * i));
+      }
+    }
+  };
+  auto store_tile = [&](int u, int p) {  // rows of output tile p from buffer u
+    if (!DMA) {
+      store_tile_part<TY, NT>(reinterpret_cast<TY*>(a.y), xb[u], b, (int64_t)p * TILE_T, d0, a.L, a.D, tid);
+      return;
+    }
+    char* dst = yw + (int64_t)p * (TILE_T * rowb);
+    constexpr int SB = GPL < 4 ? GPL : 4;  // row groups per batch of LDS reads
+#pragma unroll
+    for (int i0 = 0; i0 < GPL; i0 += SB) {
+      u32x4 v[SB];
+#pragma unroll
+      for (int i = 0; i < SB; ++i) {
+        const uint2* s = reinterpret_cast<const uint2*>(xb[u] + XTile<XE>::group(wave + NW * (i0 + i)) + lane * 16);
+        const uint2 lo = s[0], hi = s[1];
+        v[i] = u32x4{lo.x, lo.y, hi.x, hi.y};
+      }
+#pragma unroll
+      for (int i = 0; i < SB; ++i)
+        if (p < Pfull || piece_in(p, i0 + i))
+          st_row16(dst + (int64_t)(8 * NW * (i0 + i)) * rowb, lane_off(i0 + i), v[i]);
     }
   };
   // this lane's words of the published aggregate of segment j
-  auto a_slot = [&](int64_t j) { return a.agg + ((((size_t)chain * G_ + j) * NW + wave) * 64 + lane) * NG; };
+  auto a_slot = [&](int j) { return a.agg + (((size_t)chain * G_ + j) * NW + wave) * 64 + lane; };
 
   // ---- arrival, the first tile, the tables ----------------------------------
   // In static order the j-th work-group of a chain by block index takes segment
@@ -1052,8 +1075,8 @@ __global__ __launch_bounds__(StreamGeo<TX>::NT, 1) void fwd_stream_kernel(Stream
   // skipped) and the chain's first tile loads at once.
   const bool phaseA = G_ > 1;
   {
-    const int64_t e0 = phaseA ? seg_start(rank + 1) - 1 : 0;
-    if (is_ld && tile_full(e0)) load_tile(0, e0);
+    const int e0 = phaseA ? seg_start((int)rank + 1) - 1 : 0;
+    if (DMA) load_tile(0, e0);
   }
   char* stg = xb[1];  // the tables are staged in buffers 1 .. 3
   build_tables<TX>(a, d0, stg, s_kc, tid, pin, Sf);
@@ -1078,25 +1101,20 @@ __global__ __launch_bounds__(StreamGeo<TX>::NT, 1) void fwd_stream_kernel(Stream
     }
   }
   __syncthreads();
-  typename PT::AOp vop[NG][4], top[NG][4];
-  typename PT::UOp uop[NG][4];
-  // mu = lambda^16 of scan lane (component ln, channel lq of group g), as
-  // (Re, -+Im): the re lane keeps -Im, the im lane +Im (cfma_pair)
+  typename PT::AOp vop[4];
+  typename PT::OOp oop[4];
+  // mu = lambda^16 of scan lane (component ln, channel lq), as (Re, -+Im): the re
+  // lane keeps -Im, the im lane +Im (cfma_pair)
   const float sgn = (ln & 1) ? 1.f : -1.f;
   auto lane_c = [&](float2 z) { return make_float2(z.x, sgn * z.y); };
-  float mur[NG], mus[NG];
 #pragma unroll
-  for (int g = 0; g < NG; ++g) {
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      f4 uu;
-      stage_operands<TX>(stg, cb + 4 * g + k, ln, lq, top[g][k], vop[g][k], uu);
-      uop[g][k] = PT::u_op(uu);
-    }
-    const float2 mu = reinterpret_cast<const float2*>(stg + TS::PW)[kmode(g) * 17 + 16];
-    mur[g] = mu.x;
-    mus[g] = sgn * mu.y;
+  for (int k = 0; k < 4; ++k) {
+    f4 uu;
+    typename PT::AOp tt;
+    stage_operands<TX>(stg, cb + k, ln, lq, tt, vop[k], uu);
+    oop[k] = PT::o_op(tt, uu);
   }
+  const float2 mu = lane_c(reinterpret_cast<const float2*>(stg + TS::PW)[kmode * 17 + 16]);
   if (tid == 0) {
     const uint32_t order = order_want == 0 ? 0u : order_old == 0 ? order_want : order_old;
     const uint32_t seg = order == 1 ? rank : order == 2 ? atomicAdd(cw, 1u) : 0u;
@@ -1113,87 +1131,57 @@ __global__ __launch_bounds__(StreamGeo<TX>::NT, 1) void fwd_stream_kernel(Stream
   __syncthreads();
   if (s_u[2] == 0) return;  // stale counters
   const bool by_ticket = s_u[2] != 1;
-  const int64_t j = s_u[0];         // this work-group's segment
-  const int64_t s = seg_start(j);   // its first tile
-  const int S = (int)(seg_start(j + 1) - s);  // its tiles
+  const int j = __builtin_amdgcn_readfirstlane((int)s_u[0]);  // this work-group's segment
+  const int s = seg_start(j);                                 // its first tile
+  const int S = seg_start(j + 1) - s;                         // its tiles
+  // byte offset in a tile buffer of the wave's channels in row 16 ln + 4 lq
+  const int xoff = XTile<XE>::off(16 * ln + 4 * lq, cb * XE);
   // ---- phase A: the segment's tiles from last to first, k-th into buffer k & 3;
   // its aggregate Aseg = sum_t lambda^(256 (e-1-t)) A_t, A_t the tile's end state
   // from a zero start.  The first three tiles of the segment stay in their
   // buffers; the fourth's buffer is left free for phase B. ---------------------
-  uint32_t issued = 0, mark[NBUF] = {0, 0, 0, 0};
-  auto tileA = [&](int k) { return s + S - 1 - k; };
-  if (!phaseA && is_ld) {
-    // phase B's first tiles in buffers 0, 1, 2 (the first loaded above)
+  if (DMA) {
+    // tiles 0, 1, 2 of the pass (phase B's first without phase A); the first is in
+    // already unless the segment came by ticket
+    if (phaseA && by_ticket) load_tile(0, s + S - 1);
 #pragma unroll
-    for (int k = 1; k < 3; ++k) {
-      if (k < S && tile_full(s + k)) {
-        load_tile(k, s + k);
-        issued += GPL;
-      }
-      mark[k] = issued;
-    }
+    for (int k = 1; k < 3; ++k)
+      if (k < S) load_tile(k, phaseA ? s + S - 1 - k : s + k);
   }
-  if (phaseA && is_ld) {
-    // the segment's last tile is in buffer 0 unless the segment came by ticket
-    mark[0] = 0;
-    if (by_ticket && tile_full(tileA(0))) {
-      load_tile(0, tileA(0));
-      issued += GPL;
-      mark[0] = issued;
-    }
-#pragma unroll
-    for (int k = 1; k < 3; ++k) {
-      if (k < S && tile_full(tileA(k))) {
-        load_tile(k, tileA(k));
-        issued += GPL;
-      }
-      mark[k] = issued;
-    }
-  }
-  float Aseg[NG];
-  double2 pw[NG];  // lambda^(256 k), float64
-#pragma unroll
-  for (int g = 0; g < NG; ++g) {
-    Aseg[g] = 0.f;
-    pw[g] = make_double2(1.0, 0.0);
-  }
+  float Aseg = 0.f;
+  double2 pw = make_double2(1.0, 0.0);  // lambda^(256 k), float64
+  const bool mem_first = wave < NW / 2;
   for (int k = 0; phaseA && k < S; ++k) {
     const int u = k & (NBUF - 1);
-    const int64_t p = tileA(k);
-    if (tile_full(p)) {
-      if (is_ld) wait_vmcnt((int)(issued - mark[u]));
+    const int p = s + S - 1 - k;
+    if (DMA) {
+      // tile k is in once at most the loads of the two tiles after it are outstanding
+      if (k + 2 < S)
+        wait_vm<2 * GPL>();
+      else if (k + 1 < S)
+        wait_vm<GPL>();
+      else
+        wait_vm<0>();
     } else {
-      copy_tile<TX, NT>(xb[u], reinterpret_cast<const TX*>(a.x), b, p * TILE_T, d0, a.L, a.D, tid);
+      copy_tile<TX, NT>(xb[u], reinterpret_cast<const TX*>(a.x), b, (int64_t)p * TILE_T, d0, a.L, a.D, tid);
     }
     __syncthreads();
     // the tile three ahead, into the buffer of the previous one (read by every
     // wave before this barrier): the first half of the waves issues its loads
-    // before pass 1, the other half after it
-    auto memory = [&]() {
-      const int u3 = (k + 3) & (NBUF - 1);
-      if (k + 3 < S && tile_full(tileA(k + 3))) {
-        load_tile(u3, tileA(k + 3));
-        issued += GPL;
-      }
-      mark[u3] = issued;
-    };
-    const bool mem_first = wave < NW / 2;
-    if (mem_first) memory();
-    const char* xt = xb[u];
+    // before the products, the other half after them
+    const bool more = DMA && k + 3 < S;
+    if (mem_first && more) load_tile((k + 3) & (NBUF - 1), p - 3);
+    typename PT::XOp xv[4];
+    float S16[16];
+    PT::gather_rows(xb[u] + xoff, xv);
+    chunk_states<TX>(xv, vop, S16);
+    float A = S16[0];
 #pragma unroll
-    for (int g = 0; g < NG; ++g) {
-      typename PT::XOp xv[4];
-      float S16[16];
-      PT::gather4(xt, cb + 4 * g, ln, lq, xv);
-      chunk_states<TX>(xv, vop[g], S16);
-      float A = S16[0];
-#pragma unroll
-      for (int n = 1; n < 16; ++n) A = cfma_pair(mur[g], mus[g], A, S16[n]);
-      // Aseg += lambda^(256 k) A; then the power moves one tile on
-      Aseg[g] = cfma_pair((float)pw[g].x, sgn * (float)pw[g].y, A, Aseg[g]);
-      pw[g] = zmul(pw[g], s_kc[kmode(g)].l256);
-    }
-    if (!mem_first) memory();
+    for (int n = 1; n < 16; ++n) A = cfma_pair(mu.x, mu.y, A, S16[n]);
+    // Aseg += lambda^(256 k) A; then the power moves one tile on
+    Aseg = cfma_pair((float)pw.x, sgn * (float)pw.y, A, Aseg);
+    pw = zmul(pw, s_kc[kmode].l256);
+    if (!mem_first && more) load_tile((k + 3) & (NBUF - 1), p - 3);
   }
 
   // ---- look-back: the state entering the segment, E, from the published states
@@ -1202,30 +1190,23 @@ __global__ __launch_bounds__(StreamGeo<TX>::NT, 1) void fwd_stream_kernel(Stream
   // P_0 = lambda^(256 S_0) h0 + Aseg_0; every other segment publishes P_j = Aseg_j.
   // (h0 is then read before anything the chain's last tile waits for, so h_out
   // may be h0's memory.) ----------------------------------------------------------
-  float E[NG];
-#pragma unroll
-  for (int g = 0; g < NG; ++g) {
-    E[g] = 0.f;
-    const int d = d0 + cb + 4 * g + lq, m = ln >> 1;
+  float E = 0.f;
+  {
+    const int d = d0 + cb + lq, m = ln >> 1;
     if (j == 0 && a.h0 != nullptr && d < a.D && m < a.M)
-      E[g] = a.h0[((size_t)(b * a.D + d) * a.M + m) * 2 + (ln & 1)];
+      E = a.h0[((size_t)(b * a.D + d) * a.M + m) * 2 + (ln & 1)];
   }
   if (G_ > 1) {
-    float Pj[NG];
-#pragma unroll
-    for (int g = 0; g < NG; ++g) {
-      const float2 z = lane_c(Sr > 0 ? s_kc[kmode(g)].hop1 : s_kc[kmode(g)].hop0);  // segment 0's hop
-      Pj[g] = j == 0 ? cfma_pair(z.x, z.y, E[g], Aseg[g]) : Aseg[g];
-    }
-    put_state<NG>(a_slot(j), Pj, TAG);
+    const float2 z = lane_c(Sr > 0 ? s_kc[kmode].hop1 : s_kc[kmode].hop0);  // segment 0's hop
+    put_state(a_slot(j), j == 0 ? cfma_pair(z.x, z.y, E, Aseg) : Aseg, TAG);
   }
   bool ok = true;
-  for (int64_t q = 0; ok && q < j; q += FB) {
-    float Aq[FB][NG];
+  for (int q = 0; ok && q < j; q += FB) {
+    float Aq[FB];
     for (uint32_t n = 0;; ++n) {
       bool mine = true;
 #pragma unroll
-      for (int i = 0; i < FB; ++i) mine = get_state<NG>(a_slot(q + i < j ? q + i : q), TAG, Aq[i]) && mine;
+      for (int i = 0; i < FB; ++i) mine = get_state(a_slot(q + i < j ? q + i : q), TAG, Aq[i]) && mine;
       if (__ballot(!mine) == 0) break;
       if (n >= SPIN_LIMIT || ((n & 63) == 63 && ld_flag(a.hdr + 4) != 0)) {
         ok = false;
@@ -1237,12 +1218,8 @@ __global__ __launch_bounds__(StreamGeo<TX>::NT, 1) void fwd_stream_kernel(Stream
 #pragma unroll
     for (int i = 0; i < FB; ++i) {
       if (q + i < j) {
-        const bool longer = q + i < Sr;  // segment q+i has Sf + 1 tiles
-#pragma unroll
-        for (int g = 0; g < NG; ++g) {
-          const float2 z = lane_c(longer ? s_kc[kmode(g)].hop1 : s_kc[kmode(g)].hop0);
-          E[g] = cfma_pair(z.x, z.y, E[g], Aq[i][g]);
-        }
+        const float2 z = lane_c(q + i < Sr ? s_kc[kmode].hop1 : s_kc[kmode].hop0);  // Sf + 1 tiles, or Sf
+        E = cfma_pair(z.x, z.y, E, Aq[i]);
       }
     }
   }
@@ -1259,115 +1236,120 @@ __global__ __launch_bounds__(StreamGeo<TX>::NT, 1) void fwd_stream_kernel(Stream
   // once that tile's rows have been read out.  Iteration m: the tile's arrival
   // and one barrier, the load of tile s+m+1, the rows of tile s+m-1 (read out of
   // LDS while pass 2 runs), pass 2 of tile s+m. ---------------------------------
-  const int U0 = phaseA ? (S - 1) & 3 : 0, U1 = phaseA ? (S - 2) & 3 : 1, U2 = phaseA ? (S - 3) & 3 : 2;
-  const int UH = phaseA ? S & 3 : 3;
-  auto ubuf = [&](int m) {
-    const int r = m % 3;
-    return r == 0 ? U0 : r == 1 ? U1 : U2;
-  };
-  float* hs = reinterpret_cast<float*>(xb[UH]) + wave * 4 * HKS;
-  const int resident = phaseA ? 3 : 0;  // tiles left in their buffers by phase A
+  int u = phaseA ? (S - 1) & 3 : 0, un = phaseA ? (S - 2) & 3 : 1, up = phaseA ? (S - 3) & 3 : 2;
+  // H: this lane's write base (scan lane: component ln of its channel; with two
+  // parts also the chunk half lq >> 1) and read base (lane (chunk ln, quarter lq)).
+  // Row n of a channel (chunk n) is 64 bytes in four pieces, piece k (components
+  // 4k .. 4k+3) in slot k ^ ((n >> 1) & 3): the 16-byte reads of eight chunks
+  // meet eight different bank quads.
+  char* const hbuf = xb[phaseA ? S & 3 : 3] + wave * (G::HW * 4);
+  auto hchan = [](int c) { return (c * HKS + 8 * (c & 1)) * 4; };
+  char* const hwr = hbuf + (HP == 2 ? hchan(lq & 1) + (lq >> 1) * 512 : lq * (HKS * 4) + 32 * (lq & 1)) + ln * 4;
+  const char* const hrd = hbuf + ln * 64 + ((lq ^ ((ln >> 1) & 3)) << 4);
   for (int m = 0; m < S; ++m) {
-    const int64_t p = s + m;
-    const int u = ubuf(m);
-    if (m >= resident) {
-      if (tile_full(p)) {
-        if (is_ld) wait_vmcnt((int)(issued - mark[u]));
-      } else {
-        copy_tile<TX, NT>(xb[u], reinterpret_cast<const TX*>(a.x), b, p * TILE_T, d0, a.L, a.D, tid);
-      }
+    const int p = s + m;
+    if (DMA) {
+      // every tile but those phase A left (or that were loaded at the start)
+      // is the wave's latest memory operation
+      if (!phaseA && m == 1 && S > 2)
+        wait_vm<GPL>();
+      else if (m >= (phaseA ? 3 : 1))
+        wait_vm<0>();
+    } else if (!phaseA || m >= 3) {
+      copy_tile<TX, NT>(xb[u], reinterpret_cast<const TX*>(a.x), b, (int64_t)p * TILE_T, d0, a.L, a.D, tid);
     }
     // the tile is in; the rows of tile s+m-2 have been read out of its buffer;
     // every wave is done with H and with the outputs of tile s+m-1
     __syncthreads();
     // the rows of tile s+m-1 and the load of tile s+m+1: the first half of the
-    // waves issues them before pass 2, the other half after it, so that on
-    // every SIMD one wave computes while the other issues its memory operations
-    const int un = ubuf(m + 1), up = ubuf(m + 2);  // ubuf(m - 1) == ubuf(m + 2)
+    // waves issues them before the products, the other half after them, so that
+    // on every SIMD some waves compute while others issue memory operations
     auto memory = [&]() {
-      if (!SEPY && m >= 1) {
-        store_tile(up, p - 1);
-        if (tile_full(p - 1)) issued += GPL;
-      }
-      if (m + 1 >= 3 && m + 1 < S) {
-        if (tile_full(p + 1)) {
-          load_tile(un, p + 1);
-          issued += GPL;
-        }
-        mark[un] = issued;
-      }
+      if (!SEPY && m >= 1) store_tile(up, p - 1);
+      if (DMA && m + 1 >= 3 && m + 1 < S) load_tile(un, p + 1);
     };
-    const bool mem_first = wave < NW / 2;
-    if (mem_first || !tile_full(p - 1)) memory();  // a tile that is not full is stored by every thread at once
-    const bool lastp = (p == P - 1);
-    char* xt = xb[u];
-    float tail[NG];
-#pragma unroll
-    for (int g = 0; g < NG; ++g) {
-      tail[g] = 0.f;
-      if (lastp && a.h_out != nullptr) {
-        // sum_{j <= jstar} lambda^(jstar-j) x[16 nstar + j] (before y overwrites x)
-        const int ch = cb + 4 * g + lq;
-        const float2 l1 = lane_c(s_kc[kmode(g)].lam1);
-        float t = 0.f;
-        for (int jj = 0; jj <= jstar; ++jj) {
-          const float xj = to_f32(*reinterpret_cast<const TX*>(xt + XLay<XE>::off(nstar * CHUNK + jj) + ch * XE));
-          t = cfma_pair(l1.x, l1.y, t, (ln & 1) ? 0.f : xj);
-        }
-        tail[g] = t;
+    if (mem_first || !DMA) memory();  // rows that are not pieces are stored by every thread at once
+    const bool lastp = p == P - 1 && a.h_out != nullptr;
+    char* const xt = xb[u];
+    float tail = 0.f;
+    if (lastp) {
+      // sum_{j <= jstar} lambda^(jstar-j) x[16 nstar + j] (before y overwrites x)
+      const float2 l1 = lane_c(s_kc[kmode].lam1);
+      for (int jj = 0; jj <= jstar; ++jj) {
+        const float xj = to_f32(*reinterpret_cast<const TX*>(xt + XTile<XE>::off(nstar * CHUNK + jj, (cb + lq) * XE)));
+        tail = cfma_pair(l1.x, l1.y, tail, (ln & 1) ? 0.f : xj);
       }
     }
-    // pass 2: the x operands and S of every group first, the scans (independent
-    // chains, one per group) next, then per group H through LDS and
-    // y = T x + U H.  On the chain's last tile the state entering chunk nstar
-    // is read back from the H buffer.
-    typename PT::XOp xv[NG][4];
-    float S16[NG][16];
-#pragma unroll
-    for (int g = 0; g < NG; ++g) {
-      PT::gather4(xt, cb + 4 * g, ln, lq, xv[g]);
-      chunk_states<TX>(xv[g], vop[g], S16[g]);
-    }
+    // the x operands and S, the scan, then H through LDS and y = T x + U H.  On
+    // the chain's last tile the state entering chunk nstar is read back from the
+    // H buffer.
+    typename PT::XOp xv[4];
+    float S16[16];
+    PT::gather_rows(xt + xoff, xv);
+    chunk_states<TX>(xv, vop, S16);
 #pragma unroll
     for (int n = 0; n < 16; ++n) {
+      const float nx = cfma_pair(mu.x, mu.y, E, S16[n]);
+      S16[n] = E;  // now the state entering chunk n
+      E = nx;      // at the end, the state entering the next tile
+    }
+    // H part by part: with two parts the registers of chunks n and n + 8 trade
+    // their 32-lane halves, so that a lane holds component ln of channel
+    // 2 part + (lq & 1) for the chunks of half lq >> 1
+    if (HP == 2) {
 #pragma unroll
-      for (int g = 0; g < NG; ++g) {
-        const float nx = cfma_pair(mur[g], mus[g], E[g], S16[g][n]);
-        S16[g][n] = E[g];  // now the state entering chunk n
-        E[g] = nx;         // at the end, the state entering the next tile
+      for (int n = 0; n < 8; ++n) {
+        const auto w = __builtin_amdgcn_permlane32_swap(__float_as_uint(S16[n]), __float_as_uint(S16[n + 8]), false,
+                                                        false);
+        S16[n] = __uint_as_float(w[0]);
+        S16[n + 8] = __uint_as_float(w[1]);
       }
     }
+    f4 acc[4];
 #pragma unroll
-    for (int g = 0; g < NG; ++g) {
+    for (int hp = 0; hp < HP; ++hp) {
 #pragma unroll
-      for (int n = 0; n < 16; ++n) hs[lq * HKS + n * 16 + ln] = S16[g][n];
+      for (int n = 0; n < 16 / HP; ++n) {
+        // slot ((ln >> 2) ^ ((n >> 1) & 3)): the address bits 4-5 of hwr are ln >> 2
+        const uint32_t w = (uint32_t)(size_t)(lvoid_t*)hwr ^ (uint32_t)(((n >> 1) & 3) << 4);
+        *(__attribute__((address_space(3))) float*)(size_t)(w + n * 64) = S16[(16 / HP) * hp + n];
+      }
       wave_lds_order();
-      if (lastp && a.h_out != nullptr) {
+      if (lastp && (HP == 1 || (lq >> 1) == hp)) {
         // state at t = L-1: lambda^(jstar+1) times the state entering chunk nstar, plus the tail
-        const float hn = hs[lq * HKS + nstar * 16 + ln];
-        const int d = d0 + cb + 4 * g + lq, mm = ln >> 1;
-        const float2 lt = lane_c(s_kc[kmode(g)].lamt);
-        const float hl = cfma_pair(lt.x, lt.y, hn, tail[g]);
+        const float hn = *reinterpret_cast<const float*>(
+            hbuf + (HP == 2 ? hchan(lq & 1) : lq * (HKS * 4) + 32 * (lq & 1)) + nstar * 64 +
+            (((ln >> 2) ^ ((nstar >> 1) & 3)) << 4) + (ln & 3) * 4);
+        const int d = d0 + cb + lq, mm = ln >> 1;
+        const float2 lt = lane_c(s_kc[kmode].lamt);
+        const float hl = cfma_pair(lt.x, lt.y, hn, tail);
         if (d < a.D && mm < a.M) a.h_out[((size_t)(b * a.D + d) * a.M + mm) * 2 + (ln & 1)] = hl;
       }
-      f4 acc[4];
+      f4 hb[4 / HP];
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const f4 hb = *reinterpret_cast<const f4*>(&hs[k * HKS + ln * 16 + 4 * lq]);
-        acc[k] = PT::mma_u(uop[g][k], hb, PT::mma(top[g][k], xv[g][k], zero));
-      }
+      for (int c = 0; c < 4 / HP; ++c) hb[c] = *reinterpret_cast<const f4*>(hrd + hchan(c));
       wave_lds_order();
-      if (SEPY)
-        put_y4_global(reinterpret_cast<float*>(a.y), acc, b, p * TILE_T + ln * CHUNK + lq * 4, d0 + cb + 4 * g,
-                      a.L, a.D);
-      else
-        put_y4<TY>(xt, cb + 4 * g, ln, lq, acc);
+#pragma unroll
+      for (int c = 0; c < 4 / HP; ++c) {
+        const int cc = hp * (4 / HP) + c;
+        acc[cc] = PT::out(oop[cc], xv[cc], hb[c]);
+      }
     }
-    if (!mem_first && tile_full(p - 1)) memory();
+    if (SEPY)
+      put_y4_global(reinterpret_cast<float*>(a.y), acc, b, (int64_t)p * TILE_T + ln * CHUNK + lq * 4, d0 + cb, a.L,
+                    a.D);
+    else
+      put_rows4<TY>(xt + xoff, acc);
+    if (!mem_first && DMA) memory();
+    // tile m+1 is in buffer un, tile m+2 (later) in up
+    const int ut = u;
+    u = un;
+    un = up;
+    up = ut;
   }
-  // the rows of the segment's last tile
+  // the rows of the segment's last tile (its buffer is now up)
   __syncthreads();
-  if (!SEPY) store_tile(ubuf(S - 1), s + S - 1);
+  if (!SEPY) store_tile(up, s + S - 1);
 
   // ---- the last work-group of a chain resets the chain's counters, the last
   // chain to finish the call's words ------------------------------------------
@@ -1457,7 +1439,11 @@ int fwd_stream_grid(int64_t nchains, int64_t P, int num_cus) {
 
 template <typename TX, typename TY>
 hipError_t launch_fwd_stream(const StreamArgs& a, int grid, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
-  launch_timed(fwd_stream_kernel<TX, TY>, dim3((unsigned)grid), dim3(StreamGeo<TX>::NT), st, ev0, ev1, a);
+  // fast_io: 16-byte aligned activations with rows of whole 16-byte pieces
+  if (a.fast_io)
+    launch_timed(fwd_stream_kernel<TX, TY, true>, dim3((unsigned)grid), dim3(StreamGeo<TX>::NT), st, ev0, ev1, a);
+  else
+    launch_timed(fwd_stream_kernel<TX, TY, false>, dim3((unsigned)grid), dim3(StreamGeo<TX>::NT), st, ev0, ev1, a);
   return hipGetLastError();
 }
 template hipError_t launch_fwd_stream<float, float>(const StreamArgs&, int, hipStream_t, hipEvent_t, hipEvent_t);

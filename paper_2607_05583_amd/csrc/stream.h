@@ -23,6 +23,23 @@ template <int ES> struct XLay {
   __device__ static __forceinline__ int off(int t) { return (t >> 3) * GRP + (t & 7) * XROW; }
 };
 
+// Time-major LDS tile of the single-pass forward: 256 rows of 128 bytes in eight
+// 16-byte pieces, piece k of a row of chunk n (16 rows) in slot k ^ (n & 7), and
+// for 2-byte elements the rows of chunks 8 .. 15 shifted by 8 bytes.  The operand
+// reads and output writes of 16 lanes (one row of each chunk, 4 channels) then
+// fall on different banks (8 bytes a lane over 16 chunks for bf16, 16 bytes over
+// 8 chunks for float), and a group of 8 rows stays one contiguous kilobyte for
+// the direct-to-LDS loads and row stores.
+template <int ES> struct XTile {
+  static constexpr int BYTES = TILE_T * XROW + 16;
+  // byte offset of row group g (rows 8g .. 8g+7)
+  __device__ static __forceinline__ int group(int g) { return g * (8 * XROW) + (ES == 2 ? (g >> 4) * 8 : 0); }
+  // byte offset of channel byte cb (0 .. 127) of row t
+  __device__ static __forceinline__ int off(int t, int cb) {
+    return t * XROW + (ES == 2 ? (t >> 7) * 8 : 0) + ((((cb >> 4) ^ (t >> 4)) & 7) << 4) + (cb & 15);
+  }
+};
+
 // Compiler-level ordering of LDS accesses inside one wave (the LDS executes a
 // wave's accesses in program order).
 __device__ __forceinline__ void wave_lds_order() { asm volatile("" ::: "memory"); }
@@ -55,6 +72,24 @@ template <> struct FPath<float> {
   typedef f4 UOp;
   __device__ static __forceinline__ UOp u_op(const f4& u) { return u; }
   __device__ static __forceinline__ f4 mma_u(const UOp& u, const f4& h, f4 c) { return mma_f32(u, h, c); }
+  // y = T x + U H
+  struct OOp {
+    f4 t, u;
+  };
+  __device__ static __forceinline__ OOp o_op(const AOp& t, const f4& u) { return OOp{t, u}; }
+  __device__ static __forceinline__ f4 out(const OOp& o, const XOp& x, const f4& h) {
+    const f4 zero = {0.f, 0.f, 0.f, 0.f};
+    return mma_f32(o.u, h, mma_f32(o.t, x, zero));
+  }
+  // the same from the byte address p of row 16n + 4q of an XTile
+  __device__ static __forceinline__ void gather_rows(const char* p, XOp (&xv)[4]) {
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) {
+      const f4 w = *reinterpret_cast<const f4*>(p + kk * XROW);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) xv[c][kk] = w[c];
+    }
+  }
   // the 4 consecutive channels ch0 .. ch0+3 (ch0 a multiple of 4), one 16-byte read per row
   __device__ static __forceinline__ void gather4(const char* xt, int ch0, int n, int q, XOp (&xv)[4]) {
     const char* p = xt + (2 * n + (q >> 1)) * XLay<4>::GRP + 4 * (q & 1) * XROW + ch0 * 4;
@@ -104,17 +139,16 @@ template <> struct FPath<bf16_t> {
     r.lo = __builtin_bit_cast(s4, lo);
     return r;
   }
-  __device__ static __forceinline__ f4 mma_u(const UOp& u, const f4& h, f4 c) {
-    // pairs rounded together; each remainder h - bf16(h) (exact: the two are
-    // within a factor of two) as one bf16 dot product of the rounded pair with
-    // (-1, 0) or (0, -1), accumulated onto h
+  // float32 states split into bf16 halves: pairs rounded together; each remainder
+  // h - bf16(h) (exact: the two are within a factor of two) as one bf16 dot
+  // product of the rounded pair with (-1, 0) or (0, -1), accumulated onto h
+  __device__ static __forceinline__ void split_h(const f4& h, uint32_t (&ph)[2], uint32_t (&pl)[2]) {
     typedef __bf16 b2 __attribute__((ext_vector_type(2)));
     // the two selectors live in registers: a packed bf16 operand given as a
     // 32-bit inline constant is not read as the pair written here
     uint32_t u10 = 0x0000BF80u, u01 = 0xBF800000u;
-    asm volatile("" : "+v"(u10), "+v"(u01));
+    asm("" : "+s"(u10), "+s"(u01));
     const b2 m10 = __builtin_bit_cast(b2, u10), m01 = __builtin_bit_cast(b2, u01);
-    uint32_t ph[2], pl[2];
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
       const b2 hi = {(__bf16)h[2 * i], (__bf16)h[2 * i + 1]};
@@ -123,11 +157,55 @@ template <> struct FPath<bf16_t> {
                      (__bf16)__builtin_amdgcn_fdot2_f32_bf16(hi, m01, h[2 * i + 1], false)};
       pl[i] = __builtin_bit_cast(uint32_t, lo);
     }
+  }
+  __device__ static __forceinline__ f4 mma_u(const UOp& u, const f4& h, f4 c) {
+    uint32_t ph[2], pl[2];
+    split_h(h, ph, pl);
     const s4 bh = __builtin_bit_cast(s4, make_uint2(ph[0], ph[1]));
     const s4 bl = __builtin_bit_cast(s4, make_uint2(pl[0], pl[1]));
     c = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(u.hi, bh, c, 0, 0, 0);
     c = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(u.lo, bh, c, 0, 0, 0);
     return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(u.hi, bl, c, 0, 0, 0);
+  }
+  // y = T x + U H as three 32-deep products: the contraction index is shared out
+  // so that lane (n, q) holds steps 4q .. 4q+3 of x and then components
+  // 4q .. 4q+3 of H; [Th | Uh] and [Tl | Ul] meet [x | Hh], and [Th | Uh] meets
+  // [0 | Hl].  (Not a 16-deep product for the last: accumulating a 16-deep
+  // product onto a 32-deep one right behind it gave stale sums on gfx950.)
+  struct OOp {
+    bf8 hi, lo;
+  };
+  __device__ static __forceinline__ OOp o_op(const AOp& t, const f4& u) {
+    const UOp w = u_op(u);
+    OOp o;
+    const uint2 th = __builtin_bit_cast(uint2, t.hi), tl = __builtin_bit_cast(uint2, t.lo);
+    const uint2 uh = __builtin_bit_cast(uint2, w.hi), ul = __builtin_bit_cast(uint2, w.lo);
+    o.hi = __builtin_bit_cast(bf8, make_uint4(th.x, th.y, uh.x, uh.y));
+    o.lo = __builtin_bit_cast(bf8, make_uint4(tl.x, tl.y, ul.x, ul.y));
+    return o;
+  }
+  __device__ static __forceinline__ f4 out(const OOp& o, const XOp& x, const f4& h) {
+    uint32_t ph[2], pl[2];
+    split_h(h, ph, pl);
+    const uint2 xx = __builtin_bit_cast(uint2, x);
+    const bf8 b = __builtin_bit_cast(bf8, make_uint4(xx.x, xx.y, ph[0], ph[1]));
+    const bf8 bl = __builtin_bit_cast(bf8, make_uint4(0u, 0u, pl[0], pl[1]));
+    f4 c = {0.f, 0.f, 0.f, 0.f};
+    c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(o.hi, b, c, 0, 0, 0);
+    c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(o.lo, b, c, 0, 0, 0);
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(o.hi, bl, c, 0, 0, 0);
+  }
+  // the same from the byte address p of row 16n + 4q of an XTile
+  __device__ static __forceinline__ void gather_rows(const char* p, XOp (&xv)[4]) {
+    typedef unsigned short us4 __attribute__((ext_vector_type(4)));
+    us4 w[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) w[r] = *reinterpret_cast<const us4*>(p + r * XROW);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const us4 v = {w[0][c], w[1][c], w[2][c], w[3][c]};
+      xv[c] = __builtin_bit_cast(s4, v);
+    }
   }
   // the 4 consecutive channels ch0 .. ch0+3 (ch0 a multiple of 4): element r of
   // channel c from row r (the compiler reads each row once and packs with byte
@@ -174,6 +252,19 @@ __device__ __forceinline__ float cfma_pair(float zr, float zs, float v, float ad
 __device__ __forceinline__ void lds_dma16(const void* base, uint32_t off, const void* lds) {
   const uint32_t la = (uint32_t)(size_t)(lvoid_t*)lds;
   asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "{m0}"(la) : "memory");
+}
+
+// The same from a 64-bit address per lane.
+__device__ __forceinline__ void lds_dma16_lane(const void* src, const void* lds) {
+  const uint32_t la = (uint32_t)(size_t)(lvoid_t*)lds;
+  asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"((uint64_t)src), "{m0}"(la) : "memory");
+}
+
+// Wait until at most N vector memory operations of the wave are outstanding.
+template <int N>
+__device__ __forceinline__ void wait_vm() {
+  static_assert(N >= 0 && N < 64, "a six-bit count");
+  __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
 }
 
 // Wait until at most n (0 <= n <= 63) vector memory operations of the wave are
