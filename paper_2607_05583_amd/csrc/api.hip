@@ -318,6 +318,9 @@ int mix_fwd_impl(const void* x, res_dtype_t x_dt, void* y, res_dtype_t y_dt, int
     a.agg = (uint64_t*)(base + sl.agg);
     a.ring = B * g.NB <= STREAM_RING_CHAINS ? (uint64_t*)(base + sl.ring) : nullptr;
     const int grid = fwd_stream_grid(B * g.NB, g.P, ncu > 0 ? ncu : 256);
+    a.G = grid / a.nchains;
+    a.Sf = (int)(g.P / a.G);
+    a.Sr = (int)(g.P % a.G);
     if (x_dt == RES_F32)
       e = launch_fwd_stream<float, float>(a, grid, st, ev0, ev1);
     else if (y_dt == RES_BF16)

@@ -782,50 +782,64 @@ __device__ __forceinline__ double dpp_f64(double v) {
   return __builtin_bit_cast(double, (uint64_t)lo | ((uint64_t)hi << 32));
 }
 
-// The float32 parameters of thread (k, m) = 8 k + m: channel d0 + k, mode m
-// (zeros outside D x M and for threads beyond the block's channels).
+// The float32 parameters of thread t's channel d0 + k and mode m, 8 k + m = t mod
+// 8 DW.  Outside D x M some in-range entry is read and not used (no branch, so
+// the values are waited for where they are used and not before the tile loads).
 struct ModeIn {
   float gamma, omega, amp, phase;
 };
 template <typename TX>
 __device__ __forceinline__ ModeIn load_mode(const StreamArgs& a, int d0, int tid) {
-  ModeIn r{0.f, 0.f, 0.f, 0.f};
-  const int k = tid >> 3, m = tid & 7, d = d0 + k;
-  if (tid < TabStage<TX>::DW * 8 && d < a.D && m < a.M) {
-    const int i = d * a.M + m;
-    r.gamma = a.gamma[i];
-    r.omega = a.omega[i];
-    r.amp = a.amp[i];
-    r.phase = a.phase[i];
-  }
-  return r;
+  const int k = (tid >> 3) & (TabStage<TX>::DW - 1), m = tid & 7;
+  const int d = d0 + k < a.D ? d0 + k : a.D - 1;
+  const int i = d * a.M + (m < a.M ? m : a.M - 1);
+  return ModeIn{a.gamma[i], a.omega[i], a.amp[i], a.phase[i]};
 }
 
-// The tables of channels d0 .. d0+DW-1 into the stage st (threads (k, m) =
-// 8 k + m, one per channel and mode, with their parameters pin).  lambda =
-// exp(-gamma) (cos omega, sin omega) and c = amp (cos phase, sin phase) in
-// float64, the powers lambda^j by successive products and lambda^256 by eight
-// squarings and the segment hops by binary powering of it (a relative error of
-// a few 2^-53 per product); the taps
-// K[tau] = Re sum_m c lambda^tau, summed in float64 over the eight mode lanes of
-// a channel, are rounded once.
+// The tables of channels d0 .. d0+DW-1 into the stage st, by two threads per
+// channel and mode (thread t and t + 8 DW, with their parameters pin; one thread
+// for both parts took 0.3 us longer).  lambda = exp(-gamma) (cos omega, sin omega)
+// and c = amp (cos phase, sin phase) in float64; the first forms the powers
+// lambda^j by successive products and the taps K[tau] = Re sum_m c lambda^tau
+// (summed in float64 over the eight mode lanes of a channel, rounded once), the
+// second lambda^256 by eight squarings and the segment hops by binary powering
+// of it (a relative error of a few 2^-53 per product).
 template <typename TX>
-__device__ void build_tables(const StreamArgs& a, int d0, char* st, KConst* kc, int tid, const ModeIn& pin,
-                             int64_t seg) {
+__device__ void build_tables(const StreamArgs& a, int d0, char* st, KConst* kc, int tid, const ModeIn& pin) {
   typedef TabStage<TX> S;
-  if (tid >= S::DW * 8) return;
-  const int k = tid >> 3, m = tid & 7, d = d0 + k;
-  double2 z = make_double2(0.0, 0.0), cz = z;
-  if (d < a.D && m < a.M) {
+  const int km = tid & (S::DW * 8 - 1), k = km >> 3, m = km & 7;
+  const bool valid = d0 + k < a.D && m < a.M;
+  double2 z = make_double2(0.0, 0.0);
+  if (valid) {
     double sn, cs;
     sincos((double)pin.omega, &sn, &cs);
     const double e = exp(-(double)pin.gamma);
     z = make_double2(e * cs, e * sn);
+  }
+  if (tid >= S::DW * 8) {
+    double2 l2 = z;
+#pragma unroll
+    for (int s = 0; s < 8; ++s) l2 = zmul(l2, l2);
+    // the segment hops (lambda^256)^Sf and (lambda^256)^(Sf+1) by binary powering
+    double2 zs0 = make_double2(1.0, 0.0), sq = l2;
+    for (int e = a.Sf; e > 0; e >>= 1) {
+      if (e & 1) zs0 = zmul(zs0, sq);
+      sq = zmul(sq, sq);
+    }
+    const double2 zs1 = zmul(zs0, l2);
+    kc[km].l256 = l2;
+    kc[km].hop0 = make_float2((float)zs0.x, (float)zs0.y);
+    kc[km].hop1 = make_float2((float)zs1.x, (float)zs1.y);
+    return;
+  }
+  double2 cz = make_double2(0.0, 0.0);
+  if (valid) {
+    double sn, cs;
     sincos((double)pin.phase, &sn, &cs);
     const double av = (double)pin.amp;
     cz = make_double2(av * cs, av * sn);
   }
-  float2* pw = reinterpret_cast<float2*>(st + S::PW) + tid * 17;
+  float2* pw = reinterpret_cast<float2*>(st + S::PW) + km * 17;
   double tp[16];
   double2 pj = make_double2(1.0, 0.0);
 #pragma unroll
@@ -834,29 +848,9 @@ __device__ void build_tables(const StreamArgs& a, int d0, char* st, KConst* kc, 
     if (j < 16) tp[j] = cz.x * pj.x - cz.y * pj.y;
     if (j < 16) pj = zmul(pj, z);
   }
-  double2 l2 = z;
-#pragma unroll
-  for (int s = 0; s < 8; ++s) l2 = zmul(l2, l2);
-  // the segment hops (lambda^256)^seg and (lambda^256)^(seg+1) by binary powering
-  double2 zs0 = make_double2(1.0, 0.0);
-  {
-    double2 sq = l2;
-    for (int64_t e = seg; e > 0; e >>= 1) {
-      if (e & 1) zs0 = zmul(zs0, sq);
-      sq = zmul(sq, sq);
-    }
-  }
-  const double2 zs1 = zmul(zs0, l2);
-  reinterpret_cast<float2*>(st + S::CM)[tid] = make_float2((float)cz.x, (float)cz.y);
-  {
-    KConst c;
-    c.l256 = l2;
-    c.lam1 = make_float2((float)z.x, (float)z.y);
-    c.lamt = pw[(a.last_len - 1) % CHUNK + 1];
-    c.hop0 = make_float2((float)zs0.x, (float)zs0.y);
-    c.hop1 = make_float2((float)zs1.x, (float)zs1.y);
-    kc[tid] = c;
-  }
+  reinterpret_cast<float2*>(st + S::CM)[km] = make_float2((float)cz.x, (float)cz.y);
+  kc[km].lam1 = make_float2((float)z.x, (float)z.y);
+  kc[km].lamt = pw[(a.last_len - 1) % CHUNK + 1];
   // sum over the 8 mode lanes of the channel, halving the taps at each of three
   // exchanges (DPP moves of the two halves of a float64): lane m <-> 7-m keeps
   // taps 0..7 (m < 4) or 8..15, then lane m <-> m^2 keeps a half of those by bit
@@ -988,12 +982,12 @@ __global__ __launch_bounds__(StreamGeo<TX>::NT, 1) void fwd_stream_kernel(Stream
   const int blk = chain % a.NB;
   const int d0 = blk * DW;
   const int P = (int)a.P;
-  const uint32_t G_ = gridDim.x / (uint32_t)a.nchains;  // work-groups (segments) of each chain
+  const uint32_t G_ = (uint32_t)a.G;  // work-groups (segments) of each chain
   const int kmode = (cb + lq) * 8 + (ln >> 1);  // (channel, mode) of scan lane (component ln, channel lq)
   // segment j: tiles [j Sf + min(j, Sr), ... + Sf + (j < Sr))
-  const int Sf = P / (int)G_, Sr = P % (int)G_;
+  const int Sf = a.Sf, Sr = a.Sr;
   auto seg_start = [&](int j) { return j * Sf + (j < Sr ? j : Sr); };
-  uint32_t* cw = a.chainw + 4 * (size_t)chain;  // [0] next ticket, [1] arrived, [2] order, [3] finished
+  uint32_t* cw = a.chainw + stream_chain_word(chain);  // [0] next ticket, [1] arrived, [2] order, [3] finished
   const uint32_t ep = ld_flag(a.hdr + 1);
   const uint32_t TAG = ep + 1u;
   const int nstar = (a.last_len - 1) / CHUNK, jstar = (a.last_len - 1) % CHUNK;
@@ -1061,44 +1055,44 @@ __global__ __launch_bounds__(StreamGeo<TX>::NT, 1) void fwd_stream_kernel(Stream
   // ---- arrival, the first tile, the tables ----------------------------------
   // In static order the j-th work-group of a chain by block index takes segment
   // j (static order is chosen only once all G have arrived).  Its segment's last
-  // tile loads at once (again below if the chain takes tickets); the arrival
-  // count and a first look at the chain's arrivals come back while the tables
-  // are built.
+  // tile loads at once (again below if the chain takes tickets).
   const uint32_t rank = blockIdx.x / (uint32_t)a.nchains;
   const ModeIn pin = load_mode<TX>(a, d0, tid);  // before any tile load of the wave
-  uint32_t arr = 0, arrived = 0;
-  if (tid == 0) {
-    arr = atomicAdd(cw + 1, 1u);
-    arrived = ld_flag(cw + 1);
-  }
   // With one work-group per chain there is no aggregate to publish (phase A is
   // skipped) and the chain's first tile loads at once.
   const bool phaseA = G_ > 1;
-  {
-    const int e0 = phaseA ? seg_start((int)rank + 1) - 1 : 0;
-    if (DMA) load_tile(0, e0);
+  if (DMA) load_tile(0, phaseA ? seg_start((int)rank + 1) - 1 : 0);
+  // ---- the order of the chain's segments, by a wave with the shorter part of the
+  // tables: static once every work-group of the chain has arrived, else by
+  // ticket; the first CAS decides for the chain.  More arrivals than work-groups,
+  // or a ticket past the chain's segments: the counters were not in their initial
+  // state (workspace not zeroed, or changed meanwhile); such a work-group touches
+  // nothing. ------------------------------------------------------------------
+  uint32_t arr = 0, arrived = 0;
+  const bool clerk = tid == NT - 64;
+  if (clerk) {
+    arr = atomicAdd(cw + 1, 1u);
+    arrived = ld_flag(cw + 1);
+    asm volatile("" : "+v"(arr), "+v"(arrived));
   }
   char* stg = xb[1];  // the tables are staged in buffers 1 .. 3
-  build_tables<TX>(a, d0, stg, s_kc, tid, pin, Sf);
-  // ---- the order of the chain's segments: static once every work-group of the
-  // chain has arrived, else by ticket; the first CAS decides for the chain (its
-  // answer is read after the operands are formed).  More arrivals than
-  // work-groups: the counters were not in their initial state (workspace not
-  // zeroed, or changed meanwhile); such a work-group touches nothing. ----------
-  uint32_t order_old = 0, order_want = 0;
-  if (tid == 0) {
-    if (arr >= G_) {
-      atomicOr(a.hdr, 2u);
-      order_want = 0;  // stale
-    } else {
+  build_tables<TX>(a, d0, stg, s_kc, tid, pin);
+  if (clerk) {
+    uint32_t order = 0, seg = 0;  // 0: stale
+    if (arr < G_) {
       bool all = arrived >= G_;
       for (uint32_t n = 0; !all && n < ARRIVE_WAIT; ++n) {
         __builtin_amdgcn_s_sleep(2);
         all = ld_flag(cw + 1) >= G_;
       }
-      order_want = all ? 1u : 2u;
-      order_old = atomicCAS(cw + 2, 0u, order_want);
+      const uint32_t want = all ? 1u : 2u, old = atomicCAS(cw + 2, 0u, want);
+      order = old == 0 ? want : old;
+      seg = order == 1 ? rank : atomicAdd(cw, 1u);
+      if (seg >= G_) order = 0;
     }
+    if (order == 0) atomicOr(a.hdr, 2u);
+    s_u[2] = order;
+    s_u[0] = seg;
   }
   __syncthreads();
   typename PT::AOp vop[4];
@@ -1115,16 +1109,6 @@ __global__ __launch_bounds__(StreamGeo<TX>::NT, 1) void fwd_stream_kernel(Stream
     oop[k] = PT::o_op(tt, uu);
   }
   const float2 mu = lane_c(reinterpret_cast<const float2*>(stg + TS::PW)[kmode * 17 + 16]);
-  if (tid == 0) {
-    const uint32_t order = order_want == 0 ? 0u : order_old == 0 ? order_want : order_old;
-    const uint32_t seg = order == 1 ? rank : order == 2 ? atomicAdd(cw, 1u) : 0u;
-    // a ticket past the chain's segments: the counters were not in their initial
-    // state either
-    const bool stale = order == 0 || seg >= G_;
-    if (stale && order != 0) atomicOr(a.hdr, 2u);
-    s_u[2] = stale ? 0u : order;
-    s_u[0] = seg;
-  }
   // every earlier vector memory operation of the wave has completed (the first
   // tile among them)
   __builtin_amdgcn_s_waitcnt(0x0F70);

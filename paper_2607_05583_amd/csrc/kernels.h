@@ -59,6 +59,13 @@ struct FwdArgs {
 constexpr int STREAM_RING = 4;
 constexpr int64_t STREAM_RING_CHAINS = 128;
 
+// First of a chain's four counter words (65536 chains in all).  The first 4096
+// chains have 256 bytes to themselves: the arrivals and decisions of a chain's
+// work-groups are atomics on one line each, and with 16 chains on two lines (B4
+// D256 bf16) the 256 work-groups took 10 instead of 5 thousand cycles to pass.
+__host__ __device__ inline size_t stream_chain_word(int chain) {
+  return 64 * (size_t)(chain & 4095) + 4 * (size_t)(chain >> 12);
+}
 struct StreamArgs {
   const void* x;
   void* y;
@@ -66,6 +73,7 @@ struct StreamArgs {
   int D, M;
   int NB;              // channel blocks of DW channels
   int nchains;         // B * NB
+  int G, Sf, Sr;   // work-groups of a chain; its tiles over them, quotient and remainder
   int64_t P;           // tiles per chain
   int last_len;        // valid steps of a chain's last tile
   int fast_io;         // x and y 16-byte aligned and rows a multiple of 16 bytes
@@ -77,7 +85,7 @@ struct StreamArgs {
   float* h_out;        // [B][D][M][2] or null
   uint32_t* hdr;       // [0] status (bit 0: a wait gave up, bit 1: stale counters), [1] epoch,
                        // [2] finished chains, [4] a wait of this call gave up
-  uint32_t* chainw;    // [nchains][4]: next ticket, arrived work-groups, segment order (0 open,
+  uint32_t* chainw;    // [65536][4] (stream_chain_word): next ticket, arrived work-groups, segment order (0 open,
                        // 1 static, 2 tickets), finished work-groups
   uint64_t* agg;       // [nchains][G][8 waves][64][DW / 32] published state of each segment
                        // (float | tag << 32 per word); laid out for up to P segments
