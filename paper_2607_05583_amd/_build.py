@@ -1,8 +1,11 @@
-"""Build libresonator.so (HIP kernels + C ABI) for gfx950, in-tree.
+"""Build libresonator.so (HIP kernels + C ABI) for gfx950 and the binding's native
+module ``_host.so``, in-tree.
 
 Each .hip source is compiled with hipcc to an object in ``_build/`` and the
 objects are linked into ``paper_2607_05583_amd/libresonator.so``.  Packed FP32
-instructions are disabled for all device code.
+instructions are disabled for all device code.  ``csrc/host.cpp`` (host code
+against the installed PyTorch's headers) becomes ``paper_2607_05583_amd/_host.so``,
+which finds the library beside it.
 """
 from __future__ import annotations
 
@@ -10,6 +13,7 @@ import os
 import shutil
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 PKG = os.path.dirname(os.path.abspath(__file__))
@@ -17,6 +21,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(PKG, "libresonator.so")
+HOST = os.path.join(PKG, "_host.so")
 SOURCES = ["fwd.hip", "bwd.hip", "decode.hip", "epilogue.hip", "params.hip", "quadref.hip", "gemm.hip", "proj.hip", "fftref.hip", "api.hip"]
 ARCH = "gfx950"
 
@@ -32,6 +37,16 @@ def flags():
     return [f"--offload-arch={ARCH}", "-O3", "-std=c++17", "-fPIC", "-Wall",
             "-Wno-unused-result", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
             "-I", os.path.join(ROOT, "include")]
+
+
+def host_flags():
+    import torch
+
+    t = os.path.join(os.path.dirname(torch.__file__), "include")
+    return ["-O2", "-std=c++17", "-fPIC", "-Wall", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-isystem", t,
+            "-isystem", os.path.join(t, "torch", "csrc", "api", "include"), "-isystem", "/opt/rocm/include",
+            "-isystem", sysconfig.get_paths()["include"]]
 
 
 def _run(cmd):
@@ -50,6 +65,9 @@ def build(verbose: bool = False) -> str:
     for src in SOURCES:
         obj = os.path.join(BUILD, src.replace(".hip", ".o"))
         jobs.append((src, obj, [cc, *flags(), "-c", os.path.join(CSRC, src), "-o", obj]))
+    host_obj = os.path.join(BUILD, "host.o")
+    cxx = shutil.which("g++") or "g++"
+    jobs.append(("host.cpp", host_obj, [cxx, *host_flags(), "-c", os.path.join(CSRC, "host.cpp"), "-o", host_obj]))
     with ThreadPoolExecutor(max_workers=min(len(jobs), 4)) as ex:
         results = list(ex.map(lambda j: (j[0], _run(j[2])), jobs))
     failed = [(s, e) for s, (rc, e) in results if rc != 0]
@@ -57,13 +75,22 @@ def build(verbose: bool = False) -> str:
         if verbose and e.strip():
             print(f"[{s}]\n{e}", file=sys.stderr)
     if failed:
-        raise RuntimeError("HIP compile failed:\n" + "\n".join(f"--- {s}\n{e}" for s, e in failed))
+        raise RuntimeError("compile failed:\n" + "\n".join(f"--- {s}\n{e}" for s, e in failed))
     tmp = LIB + ".tmp"
     rc, err = _run([cc, f"--offload-arch={ARCH}", "-shared", "-fPIC", "-o", tmp,
-                    *[j[1] for j in jobs], "-L/opt/rocm/lib", "-lrocblas", "-lrocfft", "-Wl,-rpath,/opt/rocm/lib"])
+                    *[j[1] for j in jobs if j[1] != host_obj], "-L/opt/rocm/lib", "-lrocblas", "-lrocfft", "-Wl,-rpath,/opt/rocm/lib"])
     if rc != 0:
         raise RuntimeError("link failed:\n" + err)
     os.replace(tmp, LIB)
+    import torch
+
+    tmp = HOST + ".tmp"
+    rc, err = _run([cxx, "-shared", "-fPIC", "-o", tmp, host_obj, "-L", PKG, "-lresonator",
+                    "-L", os.path.join(os.path.dirname(torch.__file__), "lib"), "-lc10", "-lc10_hip", "-ltorch_cpu",
+                    "-ltorch_python", "-Wl,-rpath,$ORIGIN"])
+    if rc != 0:
+        raise RuntimeError("link of the native module failed:\n" + err)
+    os.replace(tmp, HOST)
     return LIB
 
 

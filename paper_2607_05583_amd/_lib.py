@@ -145,6 +145,24 @@ def lib():
     return _lib
 
 
+_host = None
+
+
+def host():
+    """The native marshalling module (csrc/host.cpp, built beside the library)."""
+    global _host
+    if _host is None:
+        lib()
+        import torch  # noqa: F401  (its libraries are loaded first)
+
+        try:
+            from . import _host as module
+        except ImportError as e:
+            raise RuntimeError("_host.so is not built: run __graft_entry__.build() first") from e
+        _host = module
+    return _host
+
+
 def check(rc: int):
     if rc != RES_OK:
         raise ResonatorError(rc, lib().resonator_last_error().decode(errors="replace"))

@@ -39,6 +39,26 @@ def _ptr(t):
     return None if t is None else ctypes.c_void_p(t.data_ptr())
 
 
+# The plain case of the hot calls (exact contiguous GPU tensors of the documented
+# types and shapes) is marshalled by the native module, which returns None for
+# anything else; the Python code below each call then checks and reports.
+_NATIVE = None
+
+
+def _native():
+    global _NATIVE
+    if _NATIVE is None:
+        _NATIVE = _lib.host()
+    return _NATIVE
+
+
+def _done(r):
+    """A native result, or the library's error raised."""
+    if r.__class__ is int:
+        check(r)
+    return r
+
+
 def _stream(device) -> ctypes.c_void_p:
     return ctypes.c_void_p(torch.cuda.current_stream(device).cuda_stream)
 
@@ -100,6 +120,10 @@ def resonator_mix_fwd(x, gamma, omega, amp, phase, h0=None, out_dtype=None, retu
 
     ``h_out`` [B, D, M, 2] float32 receives the terminal state (it may be the
     ``h0`` tensor itself: the state is then advanced in place)."""
+    if not CHECK_FWD_STATUS:
+        r = (_NATIVE or _native()).mix_fwd(x, gamma, omega, amp, phase, h0, out_dtype, return_state, out, ws, h_out)
+        if r is not None:
+            return _done(r)
     _dev(x, "x")
     if x.dim() != 3:
         raise ValueError("x must be [B, L, D]")
@@ -133,6 +157,13 @@ def resonator_mix_fwd(x, gamma, omega, amp, phase, h0=None, out_dtype=None, retu
 
 def resonator_mix_bwd(x, dy, gamma, omega, amp, phase, h0=None, want_dh0=False, ws=None):
     """Gradients of sum(dy * y): dict with dx, dgamma, domega, damp, dphase (, dh0)."""
+    r = (_NATIVE or _native()).mix_bwd(x, dy, gamma, omega, amp, phase, h0, want_dh0, ws)
+    if r is not None:
+        r = _done(r)
+        g = {"dx": r[0], "dgamma": r[1], "domega": r[2], "damp": r[3], "dphase": r[4]}
+        if want_dh0:
+            g["dh0"] = r[5]
+        return g
     _dev(x, "x")
     _dev(dy, "dy")
     if x.shape != dy.shape or x.dtype != dy.dtype or x.dim() != 3:
@@ -161,6 +192,10 @@ def resonator_mix_bwd(x, dy, gamma, omega, amp, phase, h0=None, want_dh0=False, 
 
 def resonator_state_init(x_prompt, gamma, omega, amp, phase, out=None, ws=None):
     """Decode state after a prompt x_prompt [B, L, D] (L may be 0)."""
+    if out is None and ws is None:
+        r = (_NATIVE or _native()).state_init(x_prompt, gamma, omega, amp, phase)
+        if r is not None:
+            return _done(r)
     _dev(x_prompt, "x_prompt")
     B, L, D = x_prompt.shape
     gamma, omega, amp, phase = _params(gamma, omega, amp, phase, D)
@@ -179,6 +214,10 @@ def resonator_state_init(x_prompt, gamma, omega, amp, phase, out=None, ws=None):
 
 def resonator_decode_step(x_t, gamma, omega, amp, phase, state, out_dtype=None, out=None):
     """One decode step: updates state [B, D, M, 2] in place, returns y_t [B, D]."""
+    if out_dtype is None and out is None:
+        r = (_NATIVE or _native()).decode_step(x_t, gamma, omega, amp, phase, state)
+        if r is not None:
+            return _done(r)
     _dev(x_t, "x_t")
     _dev(state, "state")
     B, D = x_t.shape
@@ -229,6 +268,10 @@ def resonator_decode_step_tab(x_t, tab, state, out_dtype=None, out=None):
 def resonator_decode_steps(x, gamma, omega, amp, phase, state, out_dtype=None, out=None):
     """N decode steps in one launch: x [B, N, D] drives known in advance; updates
     state [B, D, M, 2] in place and returns y [B, N, D] (bitwise N decode steps)."""
+    if out_dtype is None and out is None:
+        r = (_NATIVE or _native()).decode_steps(x, gamma, omega, amp, phase, state)
+        if r is not None:
+            return _done(r)
     _dev(x, "x")
     _dev(state, "state")
     B, N, D = x.shape
@@ -329,6 +372,10 @@ def resonator_fft_reference(x, gamma, omega, amp, phase):
 
 def resonator_grouped_linear(x, W, out=None):
     """y = x W for a block-diagonal W of G groups: x [..., d_in], W [G, d_in/G, d_out/G]."""
+    if out is None:
+        r = (_NATIVE or _native()).grouped_linear(x, W)
+        if r is not None:
+            return _done(r)
     _dev(x, "x")
     _dev(W, "W")
     if W.dim() != 3 or W.dtype != x.dtype:
@@ -348,6 +395,10 @@ def resonator_grouped_linear(x, W, out=None):
 def resonator_grouped_linear2(x, W0, W1, out0=None, out1=None):
     """y0 = x W0 and y1 = x W1 for block-diagonal weights of one shape (the drive
     and the gate of Sec. 3.1), from one read of x.  Returns (y0, y1)."""
+    if out0 is None and out1 is None:
+        r = (_NATIVE or _native()).grouped_linear2(x, W0, W1)
+        if r is not None:
+            return _done(r)
     _dev(x, "x")
     _dev(W0, "W0")
     _dev(W1, "W1")
@@ -434,6 +485,10 @@ def resonator_grouped_linear_bwd_data_sum(dys, Ws, dx=None, accumulate=False):
     """dx = sum_k dys[k] W_k^T per group (the data gradients of up to three
     grouped projections of one input, summed in float32 and rounded once); with
     ``accumulate`` added to the given ``dx``.  Returns dx."""
+    if dx is None and not accumulate:
+        r = (_NATIVE or _native()).bwd_data_sum(dys, Ws)
+        if r is not None:
+            return _done(r)
     if not 1 <= len(dys) <= 3 or len(dys) != len(Ws):
         raise ValueError("need 1 to 3 gradients, one weight each")
     dy0 = dys[0]
@@ -477,6 +532,11 @@ def resonator_grouped_linear_bwd_weight_sum(x, dys, outs, dWs, accumulate=False)
     projections of x: dWs[m] (+)= sum over k with outs[k] = m of x^T dys[k] per
     group, in one pass over x (the library's MFMA kernel where it takes the shape;
     deterministic).  Returns dWs."""
+    if not accumulate:
+        r = (_NATIVE or _native()).bwd_weight_sum(x, dys, outs, dWs)
+        if r is not None:
+            _done(r)
+            return dWs
     _dev(x, "x")
     _code(x)
     n = len(dys)
@@ -812,6 +872,10 @@ def resonator_epilogue_fwd(y, gate, v, Ct, lambda_c, w, s, H, out=None):
     y, gate, v: [B, L, D] (same dtype), D = H * dh; w: [D, K] float32 (K = w.shape[1];
     w = None or K = 0 disables the local path, and v, s may then be None).
     """
+    if out is None:
+        r = (_NATIVE or _native()).epilogue_fwd(y, gate, v, Ct, lambda_c, w, s, H)
+        if r is not None:
+            return _done(r)
     _dev(y, "y"); _dev(gate, "gate")
     B, L, D = y.shape
     if gate.shape != y.shape or gate.dtype != y.dtype:
@@ -849,6 +913,10 @@ def resonator_epilogue_proj_fwd(y, gate, v, Ct, lambda_c, w, s, H, Wo, out=None,
     tensor ``z`` of y's shape is given to receive it.  Wo is [H, dh, d_out/H] of
     y's dtype; returns [B, L, d_out].  Bitwise the two separate calls; shapes it
     does not take raise (epilogue_proj_supported)."""
+    if out is None:
+        r = (_NATIVE or _native()).epilogue_proj_fwd(y, gate, v, Ct, lambda_c, w, s, H, Wo, z)
+        if r is not None:
+            return _done(r)
     _dev(y, "y"); _dev(gate, "gate"); _dev(Wo, "Wo")
     B, L, D = y.shape
     if gate.shape != y.shape or gate.dtype != y.dtype or Wo.dtype != y.dtype:
@@ -881,6 +949,10 @@ def resonator_epilogue_bwd(y, gate, v, dz, Ct, lambda_c, w, s, H, ws=None):
 
     Returns (dy, dgate, dv, dCt, dlambda_c, dw, ds); dv, dw, ds are None when K = 0.
     """
+    if ws is None:
+        r = (_NATIVE or _native()).epilogue_bwd(y, gate, v, dz, Ct, lambda_c, w, s, H)
+        if r is not None:
+            return _done(r)
     _dev(y, "y"); _dev(gate, "gate"); _dev(dz, "dz")
     B, L, D = y.shape
     K = 0 if w is None else int(w.shape[1])
