@@ -51,6 +51,14 @@ int device_cus() {
   return n;
 }
 
+hipError_t compute_units(int* n) {
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e == hipSuccess) e = hipDeviceGetAttribute(n, hipDeviceAttributeMultiprocessorCount, dev);
+  if (e == hipSuccess && *n < 1) *n = 256;
+  return e;
+}
+
 }  // namespace
 
 // Workspace of resonator_mix_fwd_noalloc: every GPU the library runs on holds
@@ -432,38 +440,30 @@ int resonator_state_init(const void* x_prompt, res_dtype_t x_dt, int64_t B, int6
   if (!ws || ws_bytes < w.total)
     return fail(RES_ERR_WORKSPACE, "workspace too small: need %zu bytes, got %zu", w.total, ws_bytes);
   if (!aligned(ws, 256)) return fail(RES_ERR_MISALIGNED, "workspace must be 256-byte aligned");
-  char* base = (char*)ws;
-  ModeScalars* scal = (ModeScalars*)(base + w.scal);
-  ModeCarry* cc = (ModeCarry*)(base + w.carryc);
-  hipError_t e =
-      x_dt == RES_BF16
-          ? launch_prep<bf16_t>(g, gamma, omega, amp, phase, false, base + w.tab, scal, cc, st)
-          : launch_prep<float>(g, gamma, omega, amp, phase, false, base + w.tab, scal, cc, st);
-  if (e != hipSuccess) return hip_fail(e, "prep launch");
-  FwdArgs a{};
+  int ncu = 0;
+  hipError_t e = compute_units(&ncu);
+  if (e != hipSuccess) return hip_fail(e, "device attribute");
+  StreamArgs a{};
   a.x = x_prompt;
-  a.y = nullptr;
   a.B = B;
   a.L = L_prompt;
   a.D = (int)D;
   a.M = (int)M;
   a.NB = g.NB;
-  a.Dp = g.Dp;
-  a.Mp = g.Mp;
+  a.nchains = (int)(B * g.NB);
   a.P = g.P;
-  a.last_len = g.last_len;
   a.fast_io = aligned(x_prompt, 16) && (D * elt_size(x_dt)) % 16 == 0;
-  a.tab = base + w.tab;
-  a.scal = scal;
-  a.cc = cc;
+  a.gamma = gamma;
+  a.omega = omega;
+  a.amp = amp;
+  a.phase = phase;
   a.h_out = state_out;
-  a.agg = base + w.agg;
-  a.car = nullptr;
-  a.alast = (float2*)(base + w.alast);
-  e = x_dt == RES_F32 ? launch_fwd_agg<float>(g, a, st) : launch_fwd_agg<bf16_t>(g, a, st);
-  if (e != hipSuccess) return hip_fail(e, "aggregate launch");
-  if ((e = launch_fwd_carry(g, a, st)) != hipSuccess) return hip_fail(e, "carry launch");
-  return RES_OK;
+  a.agg = (uint64_t*)((char*)ws + w.agg);
+  a.G = fwd_stream_grid(a.nchains, g.P, ncu) / a.nchains;
+  a.Sf = (int)(g.P / a.G);
+  a.Sr = (int)(g.P % a.G);
+  e = x_dt == RES_F32 ? launch_state<float>(a, st) : launch_state<bf16_t>(a, st);
+  return e == hipSuccess ? RES_OK : hip_fail(e, "prompt state launch");
 }
 
 int resonator_mix_bwd(const void* x, const void* dy, res_dtype_t act_dt, void* dx, int64_t B,

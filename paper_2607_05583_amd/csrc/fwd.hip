@@ -671,7 +671,7 @@ constexpr uint32_t ARRIVE_WAIT = 64;
 __device__ const uint4 zero_piece = {0u, 0u, 0u, 0u};
 
 // Element copy of a tile whose rows are not 16-byte pieces (NT threads, eight
-// loads issued together); zeros outside the tensor.
+// loads issued together); zeros outside the tensor (t0 may be negative).
 template <typename TX, int NT>
 __device__ __forceinline__ void copy_tile(char* xt, const TX* x, int64_t b, int64_t t0, int d0, int64_t L,
                                           int D, int tid) {
@@ -685,7 +685,7 @@ __device__ __forceinline__ void copy_tile(char* xt, const TX* x, int64_t b, int6
     for (int i = 0; i < NB; ++i) {
       const int t = (i0 + i * NT) / DW, c = (i0 + i * NT) % DW;
       v[i] = from_f32<TX>(0.f);
-      if (t0 + t < L && d0 + c < D) v[i] = base[(int64_t)t * D + c];
+      if ((uint64_t)(t0 + t) < (uint64_t)L && d0 + c < D) v[i] = base[(int64_t)t * D + c];
     }
 #pragma unroll
     for (int i = 0; i < NB; ++i) {
@@ -1353,6 +1353,227 @@ __global__ __launch_bounds__(StreamGeo<TX>::NT, 1) void fwd_stream_kernel(Stream
   }
 }
 
+// ---------------------------------------------------------------------------
+// Prompt state (M <= 16).  Work-group (chain, segment) of tiles counted from the
+// end of the prompt, so that the last tile ends with the last step and only the
+// oldest one is partial (zeros before t = 0): the state after the last tile is
+// the prompt's.  Per tile S = V x on MFMA, moved as in the forward's phase A, the
+// end states A_0, A_1 of the two halves from a zero start (two independent chains
+// of 8 steps), and the carried state in float64, E <- lambda^256 E + lambda^128
+// A_0 + A_1.  One segment per chain when the chains fill the device; else the
+// segments' end states are folded by state_fold_kernel.  Nothing but x is read
+// per tile: bound by HBM (B64 L1024 D256 bf16: 33.5 MB).  One kernel that builds
+// its own tables took the place of tables, tile aggregates and carry fold (28 us
+// there).
+// ---------------------------------------------------------------------------
+template <typename TX, int MG, bool DMA>
+__global__ __launch_bounds__(StreamGeo<TX>::NT, 1) void state_kernel(StreamArgs a) {
+  typedef StreamGeo<TX> G;
+  typedef FPath<TX> PT;
+  constexpr int DW = G::DW, NW = G::NW, NT = G::NT, GPL = G::GPL, XE = (int)sizeof(TX), KM = DW * 8;
+  static_assert(NT == 2 * KM, "two threads per channel and mode of a group");
+  constexpr int PP = 17;  // staged powers of a (channel, mode)
+  static_assert(KM * PP * 8 <= 3 * G::XB, "the stage fits in buffers 1 .. 3");
+  __shared__ __align__(64) char xb[G::NBUF * G::XB];
+  __shared__ double2 s_hop[MG][KM];  // lambda^128
+  auto buf = [&](int u) { return xb + u * G::XB; };
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int ln = lane & 15, lq = lane >> 4;
+  const int cb = 4 * wave;
+  const int chain = (int)(blockIdx.x % (unsigned)a.nchains), j = (int)(blockIdx.x / (unsigned)a.nchains);
+  const int64_t b = chain / a.NB;
+  const int d0 = (chain % a.NB) * DW;
+  const int s = j * a.Sf + (j < a.Sr ? j : a.Sr), S = a.Sf + (j < a.Sr ? 1 : 0);
+  const int64_t rowb = (int64_t)a.D * XE;
+  const bool block_in = d0 + DW <= a.D;
+  auto tile_t0 = [&](int p) { return a.L - (a.P - p) * TILE_T; };  // negative for a partial first tile
+  auto load_tile = [&](int u, int p) {
+    const int64_t t0 = tile_t0(p);
+    const char* src = reinterpret_cast<const char*>(a.x) + (b * a.L + t0 + 8 * wave) * rowb + (int64_t)d0 * XE;
+    const bool full = block_in && t0 >= 0;
+#pragma unroll
+    for (int i = 0; i < GPL; ++i) {
+      const int g = wave + NW * i, hsw = (g >> 1) & 7;
+      int l = lane;
+      asm volatile("" : "+v"(l));  // recomputed rather than kept live
+      const uint32_t off = (uint32_t)((l >> 3) * (int)rowb) + (uint32_t)(((l & 7) ^ hsw) << 4);
+      const char* q = src + (int64_t)(8 * NW * i) * rowb;
+      char* dst = buf(u) + XTile<XE>::group(g);
+      if (full) {
+        lds_dma16(q, off, dst);
+      } else {
+        const bool in = t0 + 8 * g + (l >> 3) >= 0 && d0 + ((l & 7) ^ hsw) * (16 / XE) < a.D;
+        lds_dma16_lane(in ? q + off : reinterpret_cast<const char*>(&zero_piece), dst);
+      }
+    }
+  };
+
+  // ---- parameters, the first tile, the powers (thread half h: mode group h; with
+  // one group the second half forms lambda^128) -------------
+  const int km = tid & (KM - 1), kk = km >> 3, half = tid / KM;
+  const int mm = (MG == 2 ? 8 * half : 0) + (km & 7);
+  const bool valid = d0 + kk < a.D && mm < a.M;
+  const int ip = valid ? (d0 + kk) * a.M + mm : 0;
+  const float gam = a.gamma[ip], omg = a.omega[ip];
+  if (DMA) load_tile(0, s);
+  float2 pf[PP];
+  {
+    double2 z = make_double2(0.0, 0.0);
+    if (valid) {
+      double sn, cs;
+      sincos((double)omg, &sn, &cs);
+      const double e = exp(-(double)gam);
+      z = make_double2(e * cs, e * sn);
+    }
+    if (MG == 2 || half == 0) {
+      double2 pj = make_double2(1.0, 0.0);
+#pragma unroll
+      for (int i = 0; i < PP; ++i) {
+        pf[i] = make_float2((float)pj.x, (float)pj.y);
+        pj = zmul(pj, z);
+      }
+    }
+    if (MG == 2 || half == 1) {
+      double2 h = z;
+#pragma unroll
+      for (int i = 0; i < 7; ++i) h = zmul(h, h);
+      s_hop[MG == 2 ? half : 0][km] = h;
+    }
+  }
+  float2* stage = reinterpret_cast<float2*>(buf(1));
+  const float sgn = (ln & 1) ? 1.f : -1.f;
+  const int kmode = (cb + lq) * 8 + (ln >> 1);  // (channel, mode) of scan lane (component ln, channel lq)
+  typename PT::AOp vop[MG][4];
+  float2 mu[MG];
+#pragma unroll
+  for (int g = 0; g < MG; ++g) {
+    if (g > 0) __syncthreads();  // the earlier group's powers have been read
+    if (half == g) {
+#pragma unroll
+      for (int i = 0; i < PP; ++i) stage[km * PP + i] = pf[i];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {  // V[i][4q+r] = Re or Im (by the parity of i) of lambda^(15 - 4q - r), mode i / 2
+      const float2* pw = stage + ((cb + c) * 8 + (ln >> 1)) * PP;
+      float v[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const float2 z = pw[15 - 4 * lq - r];
+        v[r] = (ln & 1) ? z.y : z.x;
+      }
+      vop[g][c] = PT::split_a(v);
+    }
+    const float2 z = stage[kmode * PP + 16];
+    mu[g] = make_float2(z.x, sgn * z.y);
+  }
+  double2 l256[MG], l128[MG];
+#pragma unroll
+  for (int g = 0; g < MG; ++g) {
+    l128[g] = s_hop[g][kmode];
+    l256[g] = zmul(l128[g], l128[g]);
+    l256[g].y *= sgn;
+    l128[g].y *= sgn;
+  }
+  wait_vm<0>();
+  __syncthreads();  // the stage has been read; the first tile is in
+  if (DMA) {
+#pragma unroll
+    for (int k = 1; k < 3; ++k)
+      if (k < S) load_tile(k, s + k);
+  }
+
+  const int xoff = XTile<XE>::off(16 * ln + 4 * lq, cb * XE);
+  double E[MG];
+#pragma unroll
+  for (int g = 0; g < MG; ++g) E[g] = 0.0;
+  for (int k = 0; k < S; ++k) {
+    const int u = k & (G::NBUF - 1);
+    if (DMA) {
+      if (k + 2 < S)
+        wait_vm<2 * GPL>();
+      else if (k + 1 < S)
+        wait_vm<GPL>();
+      else
+        wait_vm<0>();
+    } else {
+      copy_tile<TX, NT>(buf(u), reinterpret_cast<const TX*>(a.x), b, tile_t0(s + k), d0, a.L, a.D, tid);
+    }
+    __syncthreads();
+    // three tiles ahead, into the buffer every wave has finished with
+    if (DMA && k + 3 < S) load_tile((k + 3) & (G::NBUF - 1), s + k + 3);
+    typename PT::XOp xv[4];
+    PT::gather_rows(buf(u) + xoff, xv);
+#pragma unroll
+    for (int g = 0; g < MG; ++g) {
+      float S16[16];
+      chunk_states<TX>(xv, vop[g], S16);
+      float A0 = S16[0], A1 = S16[8];
+#pragma unroll
+      for (int n = 1; n < 8; ++n) {
+        A0 = cfma_pair(mu[g].x, mu[g].y, A0, S16[n]);
+        A1 = cfma_pair(mu[g].x, mu[g].y, A1, S16[8 + n]);
+      }
+      const double pE = dpp_f64<0xB1>(E[g]), a0 = A0, pa0 = swap_pair(A0);
+      E[g] = fma(l256[g].x, E[g], fma(l256[g].y, pE, fma(l128[g].x, a0, fma(l128[g].y, pa0, (double)A1))));
+    }
+  }
+  const int d = d0 + cb + lq;
+#pragma unroll
+  for (int g = 0; g < MG; ++g) {
+    const int m = 8 * g + (ln >> 1);
+    if (a.G > 1)
+      reinterpret_cast<double*>(a.agg)[(((size_t)chain * a.G + j) * DW + cb + lq) * (16 * MG) + 16 * g + ln] = E[g];
+    else if (d < a.D && m < a.M)
+      a.h_out[((size_t)(b * a.D + d) * a.M + m) * 2 + (ln & 1)] = (float)E[g];
+  }
+}
+
+// The prompt state from its segments' end states: 8 lanes per (row, channel,
+// mode), each folding a run of segments oldest first, then the eight weighted by
+// lambda^(256 n) of the n tiles after their run (evaluated directly) and summed in
+// a fixed order.
+__global__ __launch_bounds__(256) void state_fold_kernel(StreamArgs a, int DW, int Mp) {
+  const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) >> 3;
+  const int r = threadIdx.x & 7;
+  if (i >= a.B * a.D * a.M) return;  // whole groups of 8 lanes
+  const int m = (int)(i % a.M), d = (int)(i / a.M % a.D);
+  const int64_t b = i / a.M / a.D;
+  const size_t chain = (size_t)b * a.NB + d / DW;
+  const double gam = a.gamma[d * a.M + m], omg = a.omega[d * a.M + m];
+  auto power = [&](double n) {
+    double sn, cs;
+    sincos(omg * n, &sn, &cs);
+    const double e = exp(-gam * n);
+    return make_double2(e * cs, e * sn);
+  };
+  auto start = [&](int j) { return (double)((int64_t)j * a.Sf + (j < a.Sr ? j : a.Sr)); };
+  const int per = (a.G + 7) / 8, j0 = r * per < a.G ? r * per : a.G, j1 = j0 + per < a.G ? j0 + per : a.G;
+  const double2 h0 = power((double)TILE_T * a.Sf), h1 = power((double)TILE_T * (a.Sf + 1));
+  const double2* src = reinterpret_cast<const double2*>(a.agg) + (chain * a.G * DW + d % DW) * Mp + m;
+  double2 E = make_double2(0.0, 0.0);
+  for (int j = j0; j < j1; j += 8) {
+    double2 v[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) v[q] = src[(size_t)(j + q < j1 ? j + q : j) * DW * Mp];
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+      if (j + q < j1) E = zfma(j + q < a.Sr ? h1 : h0, E, v[q]);
+  }
+  E = zmul(power((double)TILE_T * ((double)a.P - start(j1))), E);
+#pragma unroll
+  for (int o = 1; o < 8; o <<= 1) {
+    E.x += __shfl_xor(E.x, o, 8);
+    E.y += __shfl_xor(E.y, o, 8);
+  }
+  if (r == 0) {
+    a.h_out[2 * i] = (float)E.x;
+    a.h_out[2 * i + 1] = (float)E.y;
+  }
+}
+
 __global__ void fill_zero_kernel(float* __restrict__ p, int64_t n) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) p[i] = 0.f;
@@ -1420,6 +1641,31 @@ int fwd_stream_grid(int64_t nchains, int64_t P, int num_cus) {
   if (per < 1) per = 1;
   return (int)(nchains * per);
 }
+
+template <typename TX>
+hipError_t launch_state(const StreamArgs& a, hipStream_t st) {
+  const dim3 grid((unsigned)(a.nchains * a.G)), block(StreamGeo<TX>::NT);
+  const int MG = a.M > MODES_PER_GROUP ? 2 : 1;
+  if (a.fast_io) {
+    if (MG == 1)
+      hipLaunchKernelGGL((state_kernel<TX, 1, true>), grid, block, 0, st, a);
+    else
+      hipLaunchKernelGGL((state_kernel<TX, 2, true>), grid, block, 0, st, a);
+  } else {
+    if (MG == 1)
+      hipLaunchKernelGGL((state_kernel<TX, 1, false>), grid, block, 0, st, a);
+    else
+      hipLaunchKernelGGL((state_kernel<TX, 2, false>), grid, block, 0, st, a);
+  }
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess || a.G == 1) return e;
+  const int64_t threads = a.B * a.D * a.M * 8;
+  hipLaunchKernelGGL(state_fold_kernel, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, st, a,
+                     StreamGeo<TX>::DW, MG * MODES_PER_GROUP);
+  return hipGetLastError();
+}
+template hipError_t launch_state<float>(const StreamArgs&, hipStream_t);
+template hipError_t launch_state<bf16_t>(const StreamArgs&, hipStream_t);
 
 template <typename TX, typename TY>
 hipError_t launch_fwd_stream(const StreamArgs& a, int grid, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {

@@ -65,6 +65,8 @@ template <> struct FPath<float> {
     const f4 r = {__uint_as_float(u.x), __uint_as_float(u.y), __uint_as_float(u.z), __uint_as_float(u.w)};
     return r;
   }
+  // the operand of a lane's four float32 entries
+  __device__ static __forceinline__ AOp split_a(const float (&v)[4]) { return f4{v[0], v[1], v[2], v[3]}; }
   __device__ static __forceinline__ f4 mma(const AOp& a, const XOp& x, f4 c) { return mma_f32(a, x, c); }
   // (A x)^T: lane (i, q) gets columns 4q .. 4q+3 of row i of A x
   __device__ static __forceinline__ f4 mma_t(const XOp& x, const AOp& a, f4 c) { return mma_f32(x, a, c); }
@@ -112,6 +114,17 @@ template <> struct FPath<bf16_t> {
     a.hi = __builtin_bit_cast(s4, make_uint2(u.x, u.y));
     a.lo = __builtin_bit_cast(s4, make_uint2(u.z, u.w));
     return a;
+  }
+  // the operand of a lane's four float32 entries, split into bf16 halves
+  __device__ static __forceinline__ AOp split_a(const float (&v)[4]) {
+    typedef __bf16 b4 __attribute__((ext_vector_type(4)));
+    b4 hi, lo;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      hi[i] = (__bf16)v[i];
+      lo[i] = (__bf16)(v[i] - (float)hi[i]);
+    }
+    return AOp{__builtin_bit_cast(s4, hi), __builtin_bit_cast(s4, lo)};
   }
   __device__ static __forceinline__ f4 mma(const AOp& a, const XOp& x, f4 c) {
     c = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a.hi, x, c, 0, 0, 0);
