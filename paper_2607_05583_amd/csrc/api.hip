@@ -1183,7 +1183,7 @@ int resonator_epilogue_bwd(const void* y, const void* gate, const void* v, const
     return fail(RES_ERR_INVALID_ARG, "y, gate, dz, dy, dgate, Ct, dCt and dlambda_c must be non-null");
   if (K > 0 && (!v || !w || !s || !dv || !dw || !ds))
     return fail(RES_ERR_INVALID_ARG, "v, w, s, dv, dw and ds must be non-null when K > 0");
-  const size_t need = epi_workspace_bytes(B, L, H, dh, K);
+  const size_t need = epi_workspace_min(B, L, H, dh, K);
   if (!ws || ws_bytes < need)
     return fail(RES_ERR_WORKSPACE, "workspace too small: need %zu bytes, got %zu", need, ws_bytes);
   const size_t es = elt_size(act_dt), n = (size_t)(B * L * H * dh) * es;
@@ -1203,9 +1203,9 @@ int resonator_epilogue_bwd(const void* y, const void* gate, const void* v, const
   const hipError_t e =
       act_dt == RES_BF16
           ? launch_epi_bwd<bf16_t>(y, gate, v, dz, dy, dgate, dv, B, L, (int)H, (int)dh, (int)K, Ct, lambda_c, w,
-                                   s, dCt, dlambda_c, dw, ds, part, vec, st)
+                                   s, dCt, dlambda_c, dw, ds, part, ws_bytes, vec, st)
           : launch_epi_bwd<float>(y, gate, v, dz, dy, dgate, dv, B, L, (int)H, (int)dh, (int)K, Ct, lambda_c, w, s,
-                                  dCt, dlambda_c, dw, ds, part, vec, st);
+                                  dCt, dlambda_c, dw, ds, part, ws_bytes, vec, st);
   return e == hipSuccess ? RES_OK : hip_fail(e, "epilogue backward launch");
 }
 

@@ -785,9 +785,8 @@ static unsigned epi_grid(int64_t items) {
 
 template <typename T, int CPT, int HM>
 static void tile_bwd(const void* y, const void* gate, const void* v, const void* dz, void* dy, void* dgate, void* dv,
-                     int64_t B, int64_t L, int H, int dh, int K, const float* Ct, float lambda_c, const float* w,
-                     const float* s, float* part, unsigned nparts, hipStream_t st) {
-  const int R = epi_tile_rows(true, H * dh, H, K, CPT, sizeof(T));
+                     int64_t B, int64_t L, int H, int dh, int K, int R, const float* Ct, float lambda_c,
+                     const float* w, const float* s, float* part, unsigned nparts, hipStream_t st) {
   hipLaunchKernelGGL((epi_bwd_tile_kernel<T, CPT, HM>), dim3(nparts), dim3(256),
                      epi_tile_lds(true, H * dh, H, K, CPT, sizeof(T), R), st, (const T*)y, (const T*)gate,
                      (const T*)v, (const T*)dz, (T*)dy, (T*)dgate, (T*)dv, B, L, H, dh, K, R, Ct, lambda_c, w, s,
@@ -824,24 +823,35 @@ template <typename T>
 hipError_t launch_epi_bwd(const void* y, const void* gate, const void* v, const void* dz, void* dy, void* dgate,
                           void* dv, int64_t B, int64_t L, int H, int dh, int K, const float* Ct, float lambda_c,
                           const float* w, const float* s, float* dCt, float* dlambda_c, float* dw, float* ds,
-                          float* part, int vec, hipStream_t st) {
+                          float* part, size_t ws_bytes, int vec, hipStream_t st) {
   constexpr int WIDE = tile_wide<T>(true);
-  const int64_t nblk = B * ((L + EPI_ROWS - 1) / EPI_ROWS);  // partial rows the workspace holds
+  const int64_t nblk = epi_part_rows_min(B, L);
   int64_t nparts = nblk;
   hipError_t e;
   const int cpt = epi_tile_cpt<T>(vec, H * dh, H, K, true);
   if (cpt) {
-    // one partial row per block; blocks loop over chunks, so fewer blocks than chunks
-    nparts = nblk < 1024 ? nblk : 1024;
+    // one partial row per block; blocks loop over chunks, as many blocks as chunks
+    // up to two per compute unit (the bf16 kernel's 235 registers let two run:
+    // B4 L8192 bf16 takes 52 us on 512 blocks, 63 on 1024) and up to what the
+    // workspace holds.  Chunks get shorter, down to one row per thread, while there
+    // are fewer of them than blocks: a block's time is mostly fixed (13 blocks, one
+    // per 64 rows, for [1, 777, 128] float32: 29.5 us; 195 of 4 rows: 11).
+    int R = epi_tile_rows(true, H * dh, H, K, cpt, sizeof(T));
+    const int RP = tile_geo(H * dh, cpt).RP;
+    while (R - RP >= RP && B * ((L + R - 1) / R) < 512) R -= RP;
+    const int64_t nch = B * ((L + R - 1) / R);
+    const int64_t least = epi_part_rows_min(B, L) < EPI_PARTS ? epi_part_rows_min(B, L) : EPI_PARTS;
+    const int64_t cap = epi_bytes_of_rows(EPI_PARTS, H, dh, K) <= ws_bytes || nch <= least ? EPI_PARTS : least;
+    nparts = nch < cap ? nch : cap;
     const unsigned np = (unsigned)nparts;
     if (cpt == WIDE && H <= 8)
-      tile_bwd<T, WIDE, 8>(y, gate, v, dz, dy, dgate, dv, B, L, H, dh, K, Ct, lambda_c, w, s, part, np, st);
+      tile_bwd<T, WIDE, 8>(y, gate, v, dz, dy, dgate, dv, B, L, H, dh, K, R, Ct, lambda_c, w, s, part, np, st);
     else if (cpt == WIDE)
-      tile_bwd<T, WIDE, EPI_H_MAX>(y, gate, v, dz, dy, dgate, dv, B, L, H, dh, K, Ct, lambda_c, w, s, part, np, st);
+      tile_bwd<T, WIDE, EPI_H_MAX>(y, gate, v, dz, dy, dgate, dv, B, L, H, dh, K, R, Ct, lambda_c, w, s, part, np, st);
     else if (H <= 8)
-      tile_bwd<T, 1, 8>(y, gate, v, dz, dy, dgate, dv, B, L, H, dh, K, Ct, lambda_c, w, s, part, np, st);
+      tile_bwd<T, 1, 8>(y, gate, v, dz, dy, dgate, dv, B, L, H, dh, K, R, Ct, lambda_c, w, s, part, np, st);
     else
-      tile_bwd<T, 1, EPI_H_MAX>(y, gate, v, dz, dy, dgate, dv, B, L, H, dh, K, Ct, lambda_c, w, s, part, np, st);
+      tile_bwd<T, 1, EPI_H_MAX>(y, gate, v, dz, dy, dgate, dv, B, L, H, dh, K, R, Ct, lambda_c, w, s, part, np, st);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   } else {
     const int64_t rows = B * L;
@@ -861,7 +871,7 @@ hipError_t launch_epi_bwd(const void* y, const void* gate, const void* v, const 
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   const int P = H * H + H * dh + H * dh * K;
-  double* lam_terms = reinterpret_cast<double*>(part + epi_part_floats(B, L, H, dh, K));
+  double* lam_terms = reinterpret_cast<double*>(part + ((nparts * P + 1) & ~(int64_t)1));
   hipLaunchKernelGGL(epi_bwd_reduce_kernel, dim3((unsigned)((P + 3) / 4)), dim3(256), 0, st, part, nparts, H,
                      H * dh, K, Ct, lambda_c, dCt, dw, ds, lam_terms);
   if ((e = hipGetLastError()) != hipSuccess) return e;
@@ -1086,9 +1096,9 @@ template hipError_t launch_epi_fwd<bf16_t>(const void*, const void*, const void*
                                            int, const float*, float, const float*, const float*, int, hipStream_t);
 template hipError_t launch_epi_bwd<float>(const void*, const void*, const void*, const void*, void*, void*, void*,
                                           int64_t, int64_t, int, int, int, const float*, float, const float*,
-                                          const float*, float*, float*, float*, float*, float*, int, hipStream_t);
+                                          const float*, float*, float*, float*, float*, float*, size_t, int, hipStream_t);
 template hipError_t launch_epi_bwd<bf16_t>(const void*, const void*, const void*, const void*, void*, void*, void*,
                                            int64_t, int64_t, int, int, int, const float*, float, const float*,
-                                           const float*, float*, float*, float*, float*, float*, int, hipStream_t);
+                                           const float*, float*, float*, float*, float*, float*, size_t, int, hipStream_t);
 
 }  // namespace res

@@ -13,14 +13,24 @@ enum { MODE_STATE = 0, MODE_APPLY = 1 };
 constexpr int EPI_H_MAX = 32;   // heads
 constexpr int EPI_K_MAX = 16;   // local-path taps
 constexpr int EPI_ROWS = 64;    // rows per block partial
-// floats of block partials (then H*H float64 terms) in the epilogue backward workspace
-inline int64_t epi_part_floats(int64_t B, int64_t L, int64_t H, int64_t dh, int64_t K) {
-  const int64_t nblk = B * ((L + EPI_ROWS - 1) / EPI_ROWS);
-  const int64_t P = H * H + H * dh + H * dh * K;
-  return (nblk * P + 1) & ~(int64_t)1;  // even, so the float64 terms that follow are 8-byte aligned
+// Workspace of the epilogue backward: rows of block partials (one per work-group
+// of the parameter sums), then H*H float64 terms.  The generic kernels write one
+// row per EPI_ROWS rows of activations; the tile kernel as many as it has
+// work-groups (at most EPI_PARTS), so that short inputs still fill the device.
+constexpr int64_t EPI_PARTS = 512;
+inline int64_t epi_part_cols(int64_t H, int64_t dh, int64_t K) { return H * H + H * dh + H * dh * K; }
+inline int64_t epi_part_rows_min(int64_t B, int64_t L) { return B * ((L + EPI_ROWS - 1) / EPI_ROWS); }
+inline size_t epi_bytes_of_rows(int64_t rows, int64_t H, int64_t dh, int64_t K) {
+  const int64_t f = (rows * epi_part_cols(H, dh, K) + 1) & ~(int64_t)1;  // even: the float64 terms are 8-byte aligned
+  return (size_t)f * sizeof(float) + (size_t)(H * H) * sizeof(double);
+}
+// the least workspace a call takes, and what the query returns
+inline size_t epi_workspace_min(int64_t B, int64_t L, int64_t H, int64_t dh, int64_t K) {
+  return epi_bytes_of_rows(epi_part_rows_min(B, L), H, dh, K);
 }
 inline size_t epi_workspace_bytes(int64_t B, int64_t L, int64_t H, int64_t dh, int64_t K) {
-  return (size_t)epi_part_floats(B, L, H, dh, K) * sizeof(float) + (size_t)(H * H) * sizeof(double);
+  const int64_t least = epi_part_rows_min(B, L);
+  return epi_bytes_of_rows(least > EPI_PARTS ? least : EPI_PARTS, H, dh, K);
 }
 
 // LDS tile buffers of the single-kernel forward work-group, by activation size
@@ -247,6 +257,6 @@ template <typename T>
 hipError_t launch_epi_bwd(const void* y, const void* gate, const void* v, const void* dz, void* dy, void* dgate,
                           void* dv, int64_t B, int64_t L, int H, int dh, int K, const float* Ct, float lambda_c,
                           const float* w, const float* s, float* dCt, float* dlambda_c, float* dw, float* ds,
-                          float* part, int vec, hipStream_t st);
+                          float* part, size_t ws_bytes, int vec, hipStream_t st);
 
 }  // namespace res
