@@ -245,6 +245,25 @@ PyObject* decode(PyObject*, PyObject* const* a, Py_ssize_t n) {
   END_HANDLE_TH_ERRORS
 }
 
+// (x, gamma, omega, amp, phase, state, y): N steps of time-major drives x [N, B, D] into y; True when done
+PyObject* decode_steps_tm(PyObject*, PyObject* const* a, Py_ssize_t n) {
+  HANDLE_TH_ERRORS
+  if (n != 7) return none();
+  const Tensor *x = plain(a[0]), *s = plain(a[5]), *y = plain(a[6]);
+  Params p;
+  if (!x || !s || !y || x->dim() != 3 || code(*x) < 0 || code(*y) < 0 || y->sizes() != x->sizes() ||
+      !params(a + 1, &p) || p.D != x->size(2) || !f32(*s) || !shape(*s, {x->size(1), p.D, p.M, 2}))
+    return none();
+  void* st = stream(*x);
+  const int rc = call([&] {
+    return resonator_decode_steps_tm(x->data_ptr(), (res_dtype_t)code(*x), y->data_ptr(), (res_dtype_t)code(*y),
+                                     x->size(1), x->size(0), p.D, p.M, p.gamma, p.omega, p.amp, p.phase, fpm(*s), st);
+  });
+  if (rc) return PyLong_FromLong(rc);
+  Py_RETURN_TRUE;
+  END_HANDLE_TH_ERRORS
+}
+
 // A grouped weight [G, d_in/G, d_out/G] of type dt.
 const Tensor* weight(PyObject* o, at::ScalarType dt) {
   const Tensor* w = plain(o);
@@ -380,6 +399,29 @@ PyObject* bwd_weight_sum(PyObject*, PyObject* const* a, Py_ssize_t na) {
   END_HANDLE_TH_ERRORS
 }
 
+// (x, dy, dW, accumulate): the grouped weight gradient into dW; True when done
+PyObject* bwd_weight(PyObject*, PyObject* const* a, Py_ssize_t n) {
+  HANDLE_TH_ERRORS
+  if (n != 4) return none();
+  const Tensor *x = plain(a[0]), *dy = plain(a[1]), *w = plain(a[2]);
+  bool acc;
+  if (!x || !dy || !w || x->dim() < 1 || dy->dim() < 1 || code(*x) < 0 || x->scalar_type() != dy->scalar_type() ||
+      !f32(*w) || w->dim() != 3 || !truth(a[3], &acc))
+    return none();
+  const int64_t d_in = x->size(-1), d_out = dy->size(-1), G = w->size(0);
+  if (d_in < 1 || d_out < 1 || G < 1 || d_in % G || d_out % G || !shape(*w, {G, d_in / G, d_out / G})) return none();
+  const int64_t N = dy->numel() / d_out;
+  if (x->numel() != N * d_in) return none();
+  void* st = stream(*x);
+  const int rc = call([&] {
+    return resonator_grouped_linear_bwd_weight(x->data_ptr(), dy->data_ptr(), (res_dtype_t)code(*x), fpm(*w), N, d_in,
+                                               d_out, G, acc, st);
+  });
+  if (rc) return PyLong_FromLong(rc);
+  Py_RETURN_TRUE;
+  END_HANDLE_TH_ERRORS
+}
+
 // The epilogue's arguments after the activations: (Ct, lambda_c, w, s, H) at a.
 struct EpiArgs {
   int64_t B, L, D, H, K;
@@ -493,10 +535,12 @@ PyMethodDef methods[] = {RES_FN("mix_fwd", mix_fwd),
                          RES_FN("state_init", state_init),
                          RES_FN("decode_steps", decode<true>),
                          RES_FN("decode_step", decode<false>),
+                         RES_FN("decode_steps_tm", decode_steps_tm),
                          RES_FN("grouped_linear", grouped_linear),
                          RES_FN("grouped_linear2", grouped_linear2),
                          RES_FN("bwd_data_sum", bwd_data_sum),
                          RES_FN("bwd_weight_sum", bwd_weight_sum),
+                         RES_FN("bwd_weight", bwd_weight),
                          RES_FN("epilogue_fwd", epilogue_fwd),
                          RES_FN("epilogue_proj_fwd", epilogue_proj_fwd),
                          RES_FN("epilogue_bwd", epilogue_bwd),
