@@ -99,6 +99,16 @@ int resonator_mix_fwd(const void* x, res_dtype_t x_dt, void* y, res_dtype_t y_dt
                       void* ws, size_t ws_bytes, void* stream);
 
 /*
+ * Makes a newly allocated workspace (any contents) ready for ONE call of
+ * resonator_mix_fwd with these sizes: zeros in the words that call reads before
+ * it writes them.  A workspace kept for several calls, or for other sizes, is
+ * zero-filled as a whole instead.  Errors: as resonator_mix_fwd for the sizes and
+ * the workspace.
+ */
+int resonator_fwd_workspace_init(res_dtype_t act_dt, int64_t B, int64_t L, int64_t D, int64_t M, void* ws,
+                                 size_t ws_bytes, void* stream);
+
+/*
  * Backward of resonator_mix_fwd for the loss sum(dy * y) (gradients derived from
  * the Sec. 3.1 kernel; the paper trains through autograd and prints none).
  *   x, dy  [B][L][D] of act_dt          forward drive and upstream gradient

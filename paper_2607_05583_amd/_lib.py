@@ -30,7 +30,7 @@ SYMBOLS = ("resonator_version", "resonator_workspace_bytes", "resonator_mix_fwd"
            "resonator_grouped_linear_bwd_weight", "resonator_grouped_linear_bwd_weight_sum",
            "resonator_grouped_linear_bwd_weight_sum_workspace_bytes",
            "resonator_grouped_linear_bwd_weight_split", "resonator_grouped_linear_bwd_weight_split_workspace_bytes",
-           "resonator_mix_fwd_noalloc", "resonator_mix_fwd_noalloc_max_bytes", "resonator_fwd_status",
+           "resonator_mix_fwd_noalloc", "resonator_mix_fwd_noalloc_max_bytes", "resonator_fwd_workspace_init", "resonator_fwd_status",
            "resonator_fwd_status_noalloc")
 
 _lib = None
@@ -116,6 +116,8 @@ def _declare(lib):
     lib.resonator_grouped_linear_bwd_weight_split.argtypes = [vp, vp, i32, fp, i64, i64, i64, i64, i32, vp, sz, vp]
     lib.resonator_mix_fwd_noalloc.restype = i32
     lib.resonator_mix_fwd_noalloc.argtypes = [vp, i32, vp, i32, i64, i64, i64, i64, fp, fp, fp, fp, fp, fp, vp]
+    lib.resonator_fwd_workspace_init.restype = i32
+    lib.resonator_fwd_workspace_init.argtypes = [i32, i64, i64, i64, i64, vp, sz, vp]
     lib.resonator_fwd_status.restype = i32
     lib.resonator_fwd_status.argtypes = [vp, ctypes.POINTER(ctypes.c_uint32), vp]
     lib.resonator_fwd_status_noalloc.restype = i32

@@ -397,6 +397,31 @@ int resonator_mix_fwd_noalloc(const void* x, res_dtype_t x_dt, void* y, res_dtyp
                       true);
 }
 
+int resonator_fwd_workspace_init(res_dtype_t act_dt, int64_t B, int64_t L, int64_t D, int64_t M, void* ws,
+                                 size_t ws_bytes, void* stream) {
+  const int rc = check_sizes(B, L, D, M, false);
+  if (rc) return rc;
+  if (!dtype_ok(act_dt)) return fail(RES_ERR_INVALID_ARG, "unknown dtype code");
+  const Geometry g = make_geom(act_dt, B, L, D, M);
+  const WsLayout w = make_layout(RES_OP_FWD, act_dt, g);
+  if (!ws || ws_bytes < w.total)
+    return fail(RES_ERR_WORKSPACE, "workspace too small: need %zu bytes, got %zu", w.total, ws_bytes);
+  if (!aligned(ws, 256)) return fail(RES_ERR_MISALIGNED, "workspace must be 256-byte aligned");
+  char* base = (char*)ws;
+  hipError_t e;
+  if (!stream_forward(g)) {  // the three kernels read nothing they have not written; the status word starts clear
+    e = launch_stream_init((uint32_t*)base, nullptr, nullptr, 0, 0, (hipStream_t)stream);
+  } else {
+    int ncu = 0;
+    if ((e = compute_units(&ncu)) != hipSuccess) return hip_fail(e, "device attribute");
+    const StreamLayout sl = make_stream_layout(g);
+    const int nchains = (int)(B * g.NB), grid = fwd_stream_grid(nchains, g.P, ncu);
+    e = launch_stream_init((uint32_t*)(base + sl.hdr), (uint32_t*)(base + sl.chainw), base + sl.agg, nchains,
+                           grid > nchains ? (size_t)grid * g.DW * 16 * sizeof(uint64_t) : 0, (hipStream_t)stream);
+  }
+  return e == hipSuccess ? RES_OK : hip_fail(e, "workspace initialisation launch");
+}
+
 size_t resonator_mix_fwd_noalloc_max_bytes(void) { return (size_t)RES_NOALLOC_SCRATCH_BYTES; }
 
 int resonator_fwd_status(void* ws, uint32_t* status, void* stream) {

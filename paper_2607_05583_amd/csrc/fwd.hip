@@ -1574,6 +1574,27 @@ __global__ __launch_bounds__(256) void state_fold_kernel(StreamArgs a, int DW, i
   }
 }
 
+// A new workspace made ready for one call of the single-pass forward: zeros in the
+// header, the counters of its chains and the published words it uses (agg16
+// 16-byte pieces); the rest is never read.  (Zeros all over a workspace sized for
+// one segment per tile: 6.3 us at B4 L32K D256 bf16.)
+__global__ __launch_bounds__(256) void stream_init_kernel(uint32_t* hdr, uint32_t* chainw, uint4* agg, int nchains,
+                                                          int64_t agg16) {
+  const int64_t i0 = (int64_t)blockIdx.x * 256 + threadIdx.x, step = (int64_t)gridDim.x * 256;
+  const uint4 z = {0u, 0u, 0u, 0u};
+  if (i0 < 64) hdr[i0] = 0u;
+  for (int64_t c = i0; c < nchains; c += step) *reinterpret_cast<uint4*>(chainw + stream_chain_word((int)c)) = z;
+  for (int64_t i = i0; i < agg16; i += step) agg[i] = z;
+}
+
+hipError_t launch_stream_init(uint32_t* hdr, uint32_t* chainw, void* agg, int nchains, size_t agg_bytes,
+                              hipStream_t st) {
+  const int64_t n = (int64_t)(agg_bytes / 16), work = n > nchains ? n : nchains;
+  const unsigned grid = (unsigned)(work < 256 * 1024 ? (work + 255) / 256 + (work == 0) : 1024);
+  hipLaunchKernelGGL(stream_init_kernel, dim3(grid), dim3(256), 0, st, hdr, chainw, (uint4*)agg, nchains, n);
+  return hipGetLastError();
+}
+
 __global__ void fill_zero_kernel(float* __restrict__ p, int64_t n) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) p[i] = 0.f;

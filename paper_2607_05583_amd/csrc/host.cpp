@@ -147,10 +147,14 @@ PyObject* mix_fwd(PyObject*, PyObject* const* a, Py_ssize_t n) {
   }
   if (!y.defined()) y = empty(x->sizes(), *x, odt);
   if (!ho.defined() && want_state) ho = empty({B, D, M, 2}, *x, at::kFloat);
-  if (!ws.defined())
-    ws = at::zeros({(int64_t)std::max<size_t>(nb, 256)}, at::TensorOptions().device(x->device()).dtype(at::kByte));
+  const bool own = !ws.defined();  // a workspace of this call alone
+  if (own) ws = empty({(int64_t)std::max<size_t>(nb, 256)}, *x, at::kByte);
   void* st = stream(*x);
   const int rc = call([&] {
+    if (own) {
+      const int e = resonator_fwd_workspace_init((res_dtype_t)code(*x), B, L, D, M, ws.data_ptr(), nb, st);
+      if (e) return e;
+    }
     return resonator_mix_fwd(x->data_ptr(), (res_dtype_t)code(*x), y.data_ptr(), (res_dtype_t)code(y), B, L, D, M,
                              p.gamma, p.omega, p.amp, p.phase, h0 ? fp(*h0) : nullptr,
                              ho.defined() ? fpm(ho) : nullptr, ws.data_ptr(), nb, st);

@@ -143,6 +143,8 @@ hipError_t launch_fwd_carry(const Geometry& g, const FwdArgs& a, hipStream_t st)
 // Work-groups per call of the single-pass forward, and its launch.
 template <typename TX>
 hipError_t launch_state(const StreamArgs& a, hipStream_t st);
+hipError_t launch_stream_init(uint32_t* hdr, uint32_t* chainw, void* agg, int nchains, size_t agg_bytes,
+                              hipStream_t st);
 int fwd_stream_grid(int64_t nchains, int64_t P, int num_cus);
 template <typename TX, typename TY>
 hipError_t launch_fwd_stream(const StreamArgs& a, int grid, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1);

@@ -1,0 +1,122 @@
+"""The native marshalling of the hot calls against the Python marshalling of the
+same calls (the native module switched off), and the workspace a call makes for
+itself: bitwise equal, on allocations that hold other data."""
+import pytest
+import torch
+
+from gpu_util import say
+
+pytestmark = pytest.mark.gpu
+
+
+class _Off:
+    """Stands in for the native module: takes nothing, so the Python code runs."""
+
+    def __getattr__(self, name):
+        return lambda *a: None
+
+
+@pytest.fixture
+def ops(monkeypatch):
+    from paper_2607_05583_amd import ops as _ops
+    monkeypatch.setattr(_ops, "CHECK_FWD_STATUS", False)
+    monkeypatch.setattr(_ops, "_NATIVE", _ops._native())
+    return _ops
+
+
+def _params(D, M, g):
+    r = lambda: torch.rand(D, M, device="cuda", generator=g)
+    return [r() * 0.5 + 1e-3, r() * 3, torch.randn(D, M, device="cuda", generator=g), r() * 6]
+
+
+def _flat(o):
+    if isinstance(o, torch.Tensor):
+        return [o]
+    if isinstance(o, dict):
+        o = [o[k] for k in sorted(o)]
+    return [t for e in o if e is not None for t in _flat(e)]
+
+
+def _both(monkeypatch, ops, call):
+    # memory the allocator hands out again: words of 1 (the tag of a first call) and of all ones
+    for fill in (0x01, 0xFF):
+        junk = torch.full((64 << 20,), fill, dtype=torch.uint8, device="cuda")
+        if fill == 1:
+            junk.view(torch.int64).fill_(1 << 32)
+        del junk
+        a = _flat(call())
+    monkeypatch.setattr(ops, "_NATIVE", _Off())
+    b = _flat(call())
+    assert len(a) == len(b)
+    for x, y in zip(a, b):
+        assert x.shape == y.shape and x.dtype == y.dtype and torch.equal(x, y)
+
+
+@pytest.mark.parametrize("B,L,D,M", [(1, 40, 8, 1), (2, 3000, 72, 8), (3, 1030, 65, 6), (2, 700, 64, 12)])
+@pytest.mark.parametrize("dt", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("what", ["fwd", "bwd", "state", "steps", "step"])
+def test_mixing_calls(monkeypatch, ops, what, dt, B, L, D, M):
+    say(f"native {what} B={B} L={L} D={D} M={M} {dt}")
+    g = torch.Generator(device="cuda").manual_seed(L + M)
+    prm, x = _params(D, M, g), torch.randn(B, L, D, device="cuda", generator=g).to(dt)
+    h0 = torch.randn(B, D, M, 2, device="cuda", generator=g)
+    calls = {
+        "fwd": lambda: ops.resonator_mix_fwd(x, *prm, h0=h0, return_state=True, out_dtype=torch.float32),
+        "bwd": lambda: ops.resonator_mix_bwd(x, x, *prm, h0=h0, want_dh0=True),
+        "state": lambda: ops.resonator_state_init(x, *prm),
+        "steps": lambda: (ops.resonator_decode_steps(x[:, :20].contiguous(), *prm, h := h0.clone()), h),
+        "step": lambda: (ops.resonator_decode_step(x[:, 0].contiguous(), *prm, h := h0.clone()), h),
+    }
+    _both(monkeypatch, ops, calls[what])
+
+
+@pytest.mark.parametrize("dt,dh,K", [(torch.bfloat16, 32, 4), (torch.float32, 16, 3), (torch.float32, 24, 0)])
+@pytest.mark.parametrize("save", [False, True])
+def test_block_calls(monkeypatch, ops, dt, dh, K, save):
+    H, B, L, M = 4, 2, 333, 8
+    D = H * dh
+    say(f"native block {dt} dh={dh} K={K} save={save}")
+    g = torch.Generator(device="cuda").manual_seed(dh)
+    r = lambda *s: torch.randn(*s, device="cuda", generator=g)
+    x, W = r(B, L, D).to(dt), [(r(H, dh, dh) / dh ** 0.5).to(dt) for _ in range(3)]
+    w, s = (r(D, K), r(D)) if K else (None, None)
+    args = (x, *W, *_params(D, M, g), r(H, H), 0.5, w, s, H)
+
+    def call():
+        out, saved = ops.resonator_block_fwd(*args, save=True) if save else (ops.resonator_block_fwd(*args), None)
+        return out, ops.resonator_block_bwd(*args, out, saved=saved)
+
+    _both(monkeypatch, ops, call)
+
+
+def test_refusals_keep_their_messages(ops):
+    x, prm = torch.randn(1, 8, 4, device="cuda"), [torch.rand(4, 2, device="cuda") for _ in range(4)]
+    with pytest.raises(ValueError, match="contiguous"):
+        ops.resonator_mix_fwd(x.transpose(1, 2), *prm)
+    with pytest.raises(ValueError, match="D=4"):
+        ops.resonator_mix_fwd(torch.randn(1, 8, 5, device="cuda"), *prm)
+    with pytest.raises(KeyError):
+        ops.resonator_mix_fwd(x.half(), *prm)
+    with pytest.raises(ValueError, match="workspace too small"):
+        ops.resonator_mix_fwd(x, *prm, ws=torch.zeros(16, dtype=torch.uint8, device="cuda"))
+    with pytest.raises(Exception, match="overlap"):
+        ops.resonator_mix_fwd(x, *prm, out=x)
+    with pytest.raises(ValueError, match="state must be"):
+        ops.resonator_decode_steps(x, *prm, torch.zeros(1, 4, 3, 2, device="cuda"))
+
+
+def test_decode_replay_under_capture(ops):
+    """A replay launches the graph's kernel itself; captured, it still is the graph's work."""
+    g = torch.Generator(device="cuda").manual_seed(3)
+    prm, B, N, D, M = _params(24, 5, g), 3, 7, 24, 5
+    x, s0 = torch.randn(N, B, D, device="cuda", generator=g), torch.randn(B, D, M, 2, device="cuda", generator=g)
+    live, ref = s0.clone(), s0.clone()
+    graph = ops.DecodeGraph(*prm, live, N, x_dtype=x.dtype)
+    for _ in range(3):
+        y = graph.replay(x)
+        want = ops.resonator_decode_steps(x.transpose(0, 1).contiguous(), *prm, ref)
+        torch.cuda.synchronize()
+        assert torch.equal(y, want.transpose(0, 1)) and torch.equal(live, ref)
+    graph.graph.replay()
+    want = ops.resonator_decode_steps(x.transpose(0, 1).contiguous(), *prm, ref)
+    assert torch.equal(graph.y, want.transpose(0, 1)) and torch.equal(live, ref)
