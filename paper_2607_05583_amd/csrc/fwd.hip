@@ -991,7 +991,6 @@ __global__ __launch_bounds__(StreamGeo<TX>::NT, 1) void fwd_stream_kernel(Stream
   const uint32_t ep = ld_flag(a.hdr + 1);
   const uint32_t TAG = ep + 1u;
   const int nstar = (a.last_len - 1) / CHUNK, jstar = (a.last_len - 1) % CHUNK;
-  const f4 zero = {0.f, 0.f, 0.f, 0.f};
   // With 16-byte pieces (DMA) every wave loads and stores its own row groups
   // wave + NW i of a tile; tiles below Pfull are whole, the others take the
   // pieces outside the tensor from zero_piece and do not store them.

@@ -97,8 +97,9 @@ struct StreamArgs {
                        // [2] finished chains, [4] a wait of this call gave up
   uint32_t* chainw;    // [65536][4] (stream_chain_word): next ticket, arrived work-groups, segment order (0 open,
                        // 1 static, 2 tickets), finished work-groups
-  uint64_t* agg;       // [nchains][G][8 waves][64][DW / 32] published state of each segment
-                       // (float | tag << 32 per word); laid out for up to P segments
+  uint64_t* agg;       // [nchains][G][DW / 4 waves][64] published state of each segment
+                       // (float | tag << 32 per word); laid out for up to P segments.  The
+                       // prompt state: [nchains][G][DW][modes] complex float64 end states
   uint64_t* ring;       // [nchains][STREAM_RING][8 waves][64][DW / 32] I of recent tiles, or null:
                         // no tile-to-tile chains
 };
