@@ -153,7 +153,9 @@ int resonator_fwd_status_noalloc(uint32_t* status, void* stream);
  *   - stream must belong to the calling thread's current device (NULL = that
  *     device's default stream); else RES_ERR_INVALID_ARG.
  *   - Sizes whose resonator_workspace_bytes(RES_OP_FWD, ...) exceed
- *     RES_NOALLOC_SCRATCH_BYTES return RES_ERR_WORKSPACE with nothing launched.
+ *     RES_NOALLOC_SCRATCH_BYTES return RES_ERR_WORKSPACE with nothing launched
+ *     (for M > 8 the 3 MiB that such a workspace leaves to calls with M <= 8 do
+ *     not count: the array holds them besides).
  *   - All calls on one GPU share its scratch: calls that overlap in time on one
  *     GPU (concurrent streams, several host threads) race and give wrong results;
  *     calls ordered on one stream are safe.

@@ -67,7 +67,21 @@ hipError_t compute_units(int* n) {
 // forward leaves it ready for the next).  Host code never passes this name to a
 // kernel (on the host it is only a stand-in); it uses the device address that
 // hipGetSymbolAddress gives for the current device.
-static __device__ __align__(256) unsigned char scratch[RES_NOALLOC_SCRATCH_BYTES];
+//
+// The words of a forward workspace that the single-pass forward (M <= 8) keeps
+// between calls: header, chain counters and tagged states (at most STREAM_GROUPS
+// work-groups publish one).  Every other forward leaves them alone (its tables
+// and records come after them), so one workspace serves calls of any mode count.
+namespace {
+constexpr int64_t STREAM_MAX_CHAINS = 1 << 16;
+constexpr size_t STREAM_HDR_BYTES = 256;
+constexpr size_t STREAM_CHAINW_BYTES = (size_t)STREAM_MAX_CHAINS * 4 * sizeof(uint32_t);
+constexpr size_t STREAM_KEPT_BYTES =
+    STREAM_HDR_BYTES + STREAM_CHAINW_BYTES + (size_t)STREAM_GROUPS * 64 * 16 * sizeof(uint64_t);
+}  // namespace
+// The kept words come on top, so that they take no room from the sizes that the
+// documented RES_NOALLOC_SCRATCH_BYTES serve.
+static __device__ __align__(256) unsigned char scratch[RES_NOALLOC_SCRATCH_BYTES + STREAM_KEPT_BYTES];
 
 namespace {
 
@@ -134,7 +148,6 @@ struct StreamLayout {
 // workspace (every call resets the counters it used), ahead of the tagged
 // states, so that one workspace serves calls of any shapes: a call's states
 // never land on another call's counters.
-constexpr int64_t STREAM_MAX_CHAINS = 1 << 16;
 bool stream_forward(const Geometry& g) { return g.MG == 1 && g.B * g.NB <= STREAM_MAX_CHAINS; }
 
 StreamLayout make_stream_layout(const Geometry& g) {
@@ -144,9 +157,9 @@ StreamLayout make_stream_layout(const Geometry& g) {
   const size_t state = (size_t)g.DW * 16 * sizeof(uint64_t);
   size_t off = 0;
   w.hdr = off;
-  off += 256;
+  off += STREAM_HDR_BYTES;
   w.chainw = off;
-  off += (size_t)STREAM_MAX_CHAINS * 4 * sizeof(uint32_t);
+  off += STREAM_CHAINW_BYTES;
   w.agg = off;
   off += align256(tiles * state);
   w.ring = off;
@@ -164,7 +177,7 @@ WsLayout make_layout(int op, res_dtype_t act, const Geometry& g) {
       w.total = make_stream_layout(g).total;
       return w;
     }
-    off = 256;  // header (status word), as in the single-pass layout
+    off = STREAM_KEPT_BYTES;  // the status word and the single-pass forward's words
   }
   const int nm = op == RES_OP_BWD ? bwd_mats(g.MG) : fwd_mats(g.MG);
   const size_t tiles_modes = (size_t)g.B * g.P * g.Dp * g.Mp;  // = tiles * DW * Mp
@@ -277,13 +290,15 @@ int mix_fwd_impl(const void* x, res_dtype_t x_dt, void* y, res_dtype_t y_dt, int
   const Geometry g = make_geom(x_dt, B, L, D, M);
   const WsLayout w = make_layout(RES_OP_FWD, x_dt, g);
   if (noalloc) {
-    if (w.total > (size_t)RES_NOALLOC_SCRATCH_BYTES)
+    // (the three-kernel forward's need without the kept words, its own header apart)
+    const size_t need = stream_forward(g) ? w.total : w.total - STREAM_KEPT_BYTES + STREAM_HDR_BYTES;
+    if (need > (size_t)RES_NOALLOC_SCRATCH_BYTES)
       return fail(RES_ERR_WORKSPACE,
                   "sizes need %zu bytes of workspace, more than the %zu-byte static scratch of "
                   "resonator_mix_fwd_noalloc; call resonator_mix_fwd with a workspace",
-                  w.total, (size_t)RES_NOALLOC_SCRATCH_BYTES);
+                  need, (size_t)RES_NOALLOC_SCRATCH_BYTES);
     if ((rc = noalloc_scratch(stream, &ws))) return rc;
-    ws_bytes = (size_t)RES_NOALLOC_SCRATCH_BYTES;
+    ws_bytes = sizeof scratch;
   }
   if (!ws || ws_bytes < w.total)
     return fail(RES_ERR_WORKSPACE, "workspace too small: need %zu bytes, got %zu", w.total, ws_bytes);

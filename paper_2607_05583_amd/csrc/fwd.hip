@@ -1655,6 +1655,7 @@ int fwd_stream_grid(int64_t nchains, int64_t P, int num_cus) {
   // every work-group of a chain resident at once (one per compute unit), and
   // no more of them than the chain has tiles; one per chain when there are more
   // chains than compute units (a chain is then served by one work-group alone)
+  if (num_cus > STREAM_GROUPS) num_cus = STREAM_GROUPS;
   if (nchains >= num_cus) return (int)nchains;
   int64_t per = num_cus / nchains;
   if (per > P) per = P;

@@ -146,6 +146,8 @@ template <typename TX>
 hipError_t launch_state(const StreamArgs& a, hipStream_t st);
 hipError_t launch_stream_init(uint32_t* hdr, uint32_t* chainw, void* agg, int nchains, size_t agg_bytes,
                               hipStream_t st);
+// At most STREAM_GROUPS of them share chains (and publish states).
+constexpr int STREAM_GROUPS = 256;
 int fwd_stream_grid(int64_t nchains, int64_t P, int num_cus);
 template <typename TX, typename TY>
 hipError_t launch_fwd_stream(const StreamArgs& a, int grid, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1);

@@ -43,6 +43,16 @@ def test_version_and_workspace_sizes():
     assert ws(L.RES_OP_FWD, L.RES_F32, 2, 4096, 64, 8) > ws(L.RES_OP_FWD, L.RES_F32, 1, 4096, 64, 8)
 
 
+def test_forward_workspaces_keep_the_counters_apart():
+    """A forward with more than 8 modes leaves the first 256 bytes (status), the
+    1 MiB of chain counters and the 2 MiB of tagged states (256 work-groups of
+    8 KiB) to the calls with at most 8 modes that share its workspace."""
+    ws = L.lib().resonator_workspace_bytes
+    for M in (9, 16):
+        assert ws(L.RES_OP_FWD, L.RES_F32, 1, 16, 4, M) > 256 + (1 << 20) + (2 << 20)
+    assert ws(L.RES_OP_FWD, L.RES_BF16, 70000, 16, 64, 8) > 256 + (1 << 20) + (2 << 20)  # beyond 65536 chains
+
+
 FAKE = ctypes.c_void_p(0x7F0000000000)      # never dereferenced: validation fails first
 FAKE2 = ctypes.c_void_p(0x7F0100000000)
 

@@ -242,6 +242,38 @@ def test_workspace_reused_across_shapes():
         assert rel_err(host(hout), hr) <= (1e-4 if act == "f32" else 2e-2)
 
 
+@pytest.mark.parametrize("noalloc", [False, True])
+def test_workspace_shared_by_both_forwards(noalloc):
+    """Calls with more than 8 modes between calls with at most 8, on one zero-filled
+    workspace and on the static scratch: the tables and records of the former leave
+    the counters and tagged states of the latter alone."""
+    import ctypes
+
+    from paper_2607_05583_amd import _lib
+    shapes = [(2, 3001, 70, 5, "bf16", 61), (2, 900, 96, 12, "bf16", 62), (4, 2048, 256, 8, "f32", 63),
+              (1, 1500, 72, 16, "f32", 64), (2, 3001, 70, 5, "bf16", 65), (1, 8192, 64, 9, "bf16", 66),
+              (1, 8192, 64, 8, "bf16", 67)]
+    ws = torch.zeros(max(ops.workspace_bytes(ops.RES_OP_FWD, torch.float32 if act == "f32" else torch.bfloat16,
+                                             B, L, D, M) for B, L, D, M, act, _ in shapes),
+                     dtype=torch.uint8, device="cuda")
+    for B, L, D, M, act, seed in shapes:
+        say(f"workspace of both forwards B={B} L={L} D={D} M={M} {act} noalloc={noalloc}")
+        prob = W.random_problem(seed, B, L, D, M, act=act, gamma_range=(1e-4, 1.0), gamma_log=True)
+        x, pr = dev_act(prob["x"], act), params_dev(prob)
+        if noalloc:
+            y = torch.empty_like(x)
+            p = lambda t: ctypes.c_void_p(t.data_ptr())
+            code = ops._code(x)
+            _lib.check(_lib.lib().resonator_mix_fwd_noalloc(
+                p(x), code, p(y), code, B, L, D, M, *map(p, pr), None, None,
+                ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)))
+        else:
+            y = ops.resonator_mix_fwd(x, *pr, ws=ws)
+            assert ops.resonator_fwd_status(ws) == 0
+        yr, _ = O.mix_recurrence(act64(prob["x"], act), *params_np(prob))
+        assert rel_err(host(y), yr) <= tol(act, act)
+
+
 # Counter words of the single-pass forward's workspace (kernels.h, StreamArgs):
 # a 256-byte header, then four 32-bit words per chain (next ticket, arrived
 # work-groups, tile order, finished work-groups).
