@@ -126,7 +126,7 @@ PyObject* mix_fwd(PyObject*, PyObject* const* a, Py_ssize_t n) {
   Tensor y, ws, ho;
   if (a[8] != Py_None) {
     const Tensor* o = plain(a[8]);
-    if (!o || code(*o) < 0) return none();
+    if (!o || code(*o) < 0 || o->numel() < x->numel()) return none();
     y = *o;
   }
   at::ScalarType odt = x->scalar_type();

@@ -35,6 +35,16 @@ def _dev(t: torch.Tensor, name: str) -> torch.Tensor:
     return t
 
 
+def _given(t: torch.Tensor, name: str, n: int, dtype=None) -> torch.Tensor:
+    """A caller's output tensor that can take n elements (of ``dtype``)."""
+    _dev(t, name)
+    if dtype is not None and t.dtype != dtype:
+        raise ValueError(f"{name} must be {dtype} (got {t.dtype})")
+    if t.numel() < n:
+        raise ValueError(f"{name} is too small: {t.numel()} elements, {n} are written")
+    return t
+
+
 def _ptr(t):
     return None if t is None else ctypes.c_void_p(t.data_ptr())
 
@@ -131,8 +141,7 @@ def resonator_mix_fwd(x, gamma, omega, amp, phase, h0=None, out_dtype=None, retu
     gamma, omega, amp, phase = _params(gamma, omega, amp, phase, D)
     M = gamma.shape[1]
     out_dtype = x.dtype if out_dtype is None else out_dtype
-    y = out if out is not None else torch.empty((B, L, D), dtype=out_dtype, device=x.device)
-    _dev(y, "out")
+    y = _given(out, "out", x.numel()) if out is not None else torch.empty((B, L, D), dtype=out_dtype, device=x.device)
     if h_out is not None:
         _dev(h_out, "h_out")
         if h_out.dtype != torch.float32 or tuple(h_out.shape) != (B, D, M, 2):
@@ -200,8 +209,10 @@ def resonator_state_init(x_prompt, gamma, omega, amp, phase, out=None, ws=None):
     B, L, D = x_prompt.shape
     gamma, omega, amp, phase = _params(gamma, omega, amp, phase, D)
     M = gamma.shape[1]
-    st = out if out is not None else torch.empty((B, D, M, 2), dtype=torch.float32,
-                                                  device=x_prompt.device)
+    if out is not None:
+        st = _given(out, "out", B * D * M * 2, torch.float32)
+    else:
+        st = torch.empty((B, D, M, 2), dtype=torch.float32, device=x_prompt.device)
     if L > 0:
         w, n = _workspace(RES_OP_STATE_INIT, x_prompt.dtype, B, L, D, M, x_prompt.device, ws)
     else:
@@ -226,7 +237,7 @@ def resonator_decode_step(x_t, gamma, omega, amp, phase, state, out_dtype=None, 
     if state.dtype != torch.float32 or tuple(state.shape) != (B, D, M, 2):
         raise ValueError("state must be float32 [B, D, M, 2]")
     out_dtype = x_t.dtype if out_dtype is None else out_dtype
-    y = out if out is not None else torch.empty((B, D), dtype=out_dtype, device=x_t.device)
+    y = _given(out, "out", B * D) if out is not None else torch.empty((B, D), dtype=out_dtype, device=x_t.device)
     check(_lib.lib().resonator_decode_step(
         _ptr(x_t), _code(x_t), _ptr(y), _code(y), B, D, M, _ptr(gamma), _ptr(omega), _ptr(amp),
         _ptr(phase), _ptr(state), _stream(x_t.device)))
@@ -259,7 +270,7 @@ def resonator_decode_step_tab(x_t, tab, state, out_dtype=None, out=None):
     if state.dtype != torch.float32 or tuple(state.shape) != (B, D, M, 2):
         raise ValueError("state must be float32 [B, D, M, 2]")
     out_dtype = x_t.dtype if out_dtype is None else out_dtype
-    y = out if out is not None else torch.empty((B, D), dtype=out_dtype, device=x_t.device)
+    y = _given(out, "out", B * D) if out is not None else torch.empty((B, D), dtype=out_dtype, device=x_t.device)
     check(_lib.lib().resonator_decode_step_tab(_ptr(x_t), _code(x_t), _ptr(y), _code(y), B, D, M, _ptr(tab),
                                                _ptr(state), _stream(x_t.device)))
     return y
@@ -280,7 +291,7 @@ def resonator_decode_steps(x, gamma, omega, amp, phase, state, out_dtype=None, o
     if state.dtype != torch.float32 or tuple(state.shape) != (B, D, M, 2):
         raise ValueError("state must be float32 [B, D, M, 2]")
     out_dtype = x.dtype if out_dtype is None else out_dtype
-    y = out if out is not None else torch.empty((B, N, D), dtype=out_dtype, device=x.device)
+    y = _given(out, "out", x.numel()) if out is not None else torch.empty((B, N, D), dtype=out_dtype, device=x.device)
     check(_lib.lib().resonator_decode_steps(
         _ptr(x), _code(x), _ptr(y), _code(y), B, N, D, M, _ptr(gamma), _ptr(omega), _ptr(amp),
         _ptr(phase), _ptr(state), _stream(x.device)))
@@ -392,8 +403,10 @@ def resonator_grouped_linear(x, W, out=None):
     if d_in != G * di:
         raise ValueError(f"x has {d_in} features, W expects {G * di}")
     N = x.numel() // d_in
-    y = out if out is not None else torch.empty(x.shape[:-1] + (G * dq,), dtype=x.dtype, device=x.device)
-    _dev(y, "out")
+    if out is not None:
+        y = _given(out, "out", N * G * dq, x.dtype)
+    else:
+        y = torch.empty(x.shape[:-1] + (G * dq,), dtype=x.dtype, device=x.device)
     check(_lib.lib().resonator_grouped_linear(_ptr(x), _ptr(W), _code(x), _ptr(y), N, d_in, G * dq, G,
                                               _stream(x.device)))
     return y
@@ -417,10 +430,9 @@ def resonator_grouped_linear2(x, W0, W1, out0=None, out1=None):
         raise ValueError(f"x has {d_in} features, W expects {G * di}")
     N = x.numel() // d_in
     shape = x.shape[:-1] + (G * dq,)
-    y0 = out0 if out0 is not None else torch.empty(shape, dtype=x.dtype, device=x.device)
-    y1 = out1 if out1 is not None else torch.empty(shape, dtype=x.dtype, device=x.device)
-    _dev(y0, "out0")
-    _dev(y1, "out1")
+    new = lambda: torch.empty(shape, dtype=x.dtype, device=x.device)
+    y0 = _given(out0, "out0", N * G * dq, x.dtype) if out0 is not None else new()
+    y1 = _given(out1, "out1", N * G * dq, x.dtype) if out1 is not None else new()
     check(_lib.lib().resonator_grouped_linear2(_ptr(x), _ptr(W0), _ptr(W1), _code(x), _ptr(y0), _ptr(y1), N, d_in,
                                                G * dq, G, _stream(x.device)))
     return y0, y1
@@ -626,7 +638,7 @@ def resonator_block_diag_extract(Wd, G, out=None, accumulate=False):
         raise ValueError("W_dense must hold one d_in x d_out matrix")
     W = out if out is not None else torch.empty((G, d_in // G, d_out // G), dtype=torch.float32, device=Wd.device)
     if out is not None:
-        _dev(out, "out")
+        _given(out, "out", d_in * d_out // max(G, 1), torch.float32)
     check(_lib.lib().resonator_block_diag_extract(_ptr(Wd), d_in, d_out, G, _ptr(W), int(accumulate),
                                                   _stream(Wd.device)))
     return W
@@ -900,7 +912,7 @@ def resonator_epilogue_fwd(y, gate, v, Ct, lambda_c, w, s, H, out=None):
         if v.shape != y.shape or v.dtype != y.dtype:
             raise ValueError("v must match y in shape and dtype")
     _epi_params(Ct, w, s, H, D, K)
-    z = torch.empty_like(y) if out is None else _dev(out, "out")
+    z = torch.empty_like(y) if out is None else _given(out, "out", y.numel(), y.dtype)
     check(_lib.lib().resonator_epilogue_fwd(
         _ptr(y), _ptr(gate), _ptr(v) if K else None, _code(y), _ptr(z), B, L, H, D // H, K, _ptr(Ct),
         float(lambda_c), _ptr(w) if K else None, _ptr(s) if K else None, _stream(y.device)))
@@ -944,7 +956,10 @@ def resonator_epilogue_proj_fwd(y, gate, v, Ct, lambda_c, w, s, H, Wo, out=None,
     if Wo.dim() != 3 or Wo.shape[0] != H or Wo.shape[1] != D // H:
         raise ValueError(f"Wo must be [H, dh, d_out/H] = [{H}, {D // H}, *]")
     d_out = H * Wo.shape[2]
-    o = torch.empty((B, L, d_out), dtype=y.dtype, device=y.device) if out is None else _dev(out, "out")
+    if out is not None:
+        o = _given(out, "out", B * L * d_out, y.dtype)
+    else:
+        o = torch.empty((B, L, d_out), dtype=y.dtype, device=y.device)
     if z is not None:
         _dev(z, "z")
         if z.shape != y.shape or z.dtype != y.dtype:

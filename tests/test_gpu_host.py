@@ -105,6 +105,44 @@ def test_refusals_keep_their_messages(ops):
         ops.resonator_decode_steps(x, *prm, torch.zeros(1, 4, 3, 2, device="cuda"))
 
 
+def test_outputs_that_are_too_small_are_refused(ops):
+    """A given output smaller than what the call writes raises before any launch; a
+    larger one takes the result in its first elements."""
+    B, L, D, M, H = 2, 40, 32, 3, 2
+    g = torch.Generator(device="cuda").manual_seed(9)
+    prm, x = _params(D, M, g), torch.randn(B, L, D, device="cuda", generator=g)
+    W = torch.randn(H, D // H, D // H, device="cuda", generator=g)
+    h, Ct = torch.zeros(B, D, M, 2, device="cuda"), torch.zeros(H, H, device="cuda")
+    calls = {
+        "mix": (B * L * D, lambda o: ops.resonator_mix_fwd(x, *prm, out=o)),
+        "state": (B * D * M * 2, lambda o: ops.resonator_state_init(x, *prm, out=o)),
+        "step": (B * D, lambda o: ops.resonator_decode_step(x[:, 0].contiguous(), *prm, h, out=o)),
+        "step_tab": (B * D, lambda o: ops.resonator_decode_step_tab(
+            x[:, 0].contiguous(), ops.resonator_decode_constants(*prm), h, out=o)),
+        "steps": (B * L * D, lambda o: ops.resonator_decode_steps(x, *prm, h, out=o)),
+        "linear": (B * L * D, lambda o: ops.resonator_grouped_linear(x, W, out=o)),
+        "linear2": (B * L * D, lambda o: ops.resonator_grouped_linear2(x, W, W, out0=o, out1=o.clone())),
+        "extract": (D * D // H, lambda o: ops.resonator_block_diag_extract(torch.ones(D, D, device="cuda"), H, out=o)),
+        "epilogue": (B * L * D, lambda o: ops.resonator_epilogue_fwd(x, x, None, Ct, 0.5, None, None, H, out=o)),
+        "epilogue_proj": (B * L * D, lambda o: ops.resonator_epilogue_proj_fwd(x, x, None, Ct, 0.5, None, None, H, W,
+                                                                              out=o)),
+    }
+    for name, (n, call) in calls.items():
+        say(f"given output {name}")
+        with pytest.raises(ValueError, match="too small"):
+            call(torch.empty(n - 1, device="cuda"))
+        h.zero_()
+        exact, larger = torch.empty(n, device="cuda"), torch.full((n + 64,), 7.0, device="cuda")
+        call(exact)
+        h.zero_()
+        call(larger)
+        assert torch.equal(larger[:n], exact) and bool((larger[n:] == 7.0).all())
+    with pytest.raises(ValueError, match="must be torch.float32"):
+        ops.resonator_state_init(x, *prm, out=torch.empty(B, D, M, 2, device="cuda", dtype=torch.bfloat16))
+    with pytest.raises(ValueError, match="on the GPU"):
+        ops.resonator_decode_step(x[:, 0].contiguous(), *prm, h, out=torch.empty(B, D))
+
+
 def test_decode_replay_under_capture(ops):
     """A replay launches the graph's kernel itself; captured, it still is the graph's work."""
     g = torch.Generator(device="cuda").manual_seed(3)
