@@ -14,6 +14,7 @@
 #include <Python.h>
 
 #include <ATen/Functions.h>
+#include <c10/core/DeviceGuard.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/Dtype.h>
 #include <torch/csrc/Exceptions.h>
@@ -46,7 +47,15 @@ bool f32(const Tensor& t) { return t.scalar_type() == at::kFloat; }
 bool shape(const Tensor& t, std::initializer_list<int64_t> s) { return t.sizes() == at::IntArrayRef(s); }
 const float* fp(const Tensor& t) { return static_cast<const float*>(t.data_ptr()); }
 float* fpm(const Tensor& t) { return static_cast<float*>(t.data_ptr()); }
-void* stream(const Tensor& t) { return c10::hip::getCurrentHIPStream(t.device().index()).stream(); }
+// The launch context of a call on t's GPU: that device current until the end of the
+// scope (a device's default stream is the null stream, which means the current
+// device) and its current stream.
+struct OnDevice {
+  c10::DeviceGuard guard;
+  void* stream;
+  explicit OnDevice(const Tensor& t)
+      : guard(t.device()), stream(c10::hip::getCurrentHIPStream(t.device().index()).stream()) {}
+};
 Tensor empty(at::IntArrayRef s, const Tensor& like, at::ScalarType dt) {
   return at::empty(s, at::TensorOptions().device(like.device()).dtype(dt));
 }
@@ -149,15 +158,15 @@ PyObject* mix_fwd(PyObject*, PyObject* const* a, Py_ssize_t n) {
   if (!ho.defined() && want_state) ho = empty({B, D, M, 2}, *x, at::kFloat);
   const bool own = !ws.defined();  // a workspace of this call alone
   if (own) ws = empty({(int64_t)std::max<size_t>(nb, 256)}, *x, at::kByte);
-  void* st = stream(*x);
+  const OnDevice on(*x);
   const int rc = call([&] {
     if (own) {
-      const int e = resonator_fwd_workspace_init((res_dtype_t)code(*x), B, L, D, M, ws.data_ptr(), nb, st);
+      const int e = resonator_fwd_workspace_init((res_dtype_t)code(*x), B, L, D, M, ws.data_ptr(), nb, on.stream);
       if (e) return e;
     }
     return resonator_mix_fwd(x->data_ptr(), (res_dtype_t)code(*x), y.data_ptr(), (res_dtype_t)code(y), B, L, D, M,
                              p.gamma, p.omega, p.amp, p.phase, h0 ? fp(*h0) : nullptr,
-                             ho.defined() ? fpm(ho) : nullptr, ws.data_ptr(), nb, st);
+                             ho.defined() ? fpm(ho) : nullptr, ws.data_ptr(), nb, on.stream);
   });
   if (rc) return PyLong_FromLong(rc);
   return want_state ? pack({y, ho}) : THPVariable_Wrap(y);
@@ -193,11 +202,11 @@ PyObject* mix_bwd(PyObject*, PyObject* const* a, Py_ssize_t n) {
   for (Tensor& t : g) t = empty({D, M}, *x, at::kFloat);
   if (want) dh0 = empty({B, D, M, 2}, *x, at::kFloat);
   if (!ws.defined()) ws = empty({(int64_t)std::max<size_t>(nb, 256)}, *x, at::kByte);
-  void* st = stream(*x);
+  const OnDevice on(*x);
   const int rc = call([&] {
     return resonator_mix_bwd(x->data_ptr(), dy->data_ptr(), (res_dtype_t)code(*x), dx.data_ptr(), B, L, D, M, p.gamma,
                              p.omega, p.amp, p.phase, h0 ? fp(*h0) : nullptr, fpm(g[0]), fpm(g[1]), fpm(g[2]),
-                             fpm(g[3]), want ? fpm(dh0) : nullptr, ws.data_ptr(), nb, st);
+                             fpm(g[3]), want ? fpm(dh0) : nullptr, ws.data_ptr(), nb, on.stream);
   });
   if (rc) return PyLong_FromLong(rc);
   return pack({dx, g[0], g[1], g[2], g[3], dh0});
@@ -216,10 +225,10 @@ PyObject* state_init(PyObject*, PyObject* const* a, Py_ssize_t n) {
   if (nb == 0) return none();
   const Tensor h = empty({B, D, M, 2}, *x, at::kFloat);
   const Tensor ws = empty({(int64_t)std::max<size_t>(nb, 256)}, *x, at::kByte);
-  void* st = stream(*x);
+  const OnDevice on(*x);
   const int rc = call([&] {
     return resonator_state_init(x->data_ptr(), (res_dtype_t)code(*x), B, L, D, M, p.gamma, p.omega, p.amp, p.phase,
-                                fpm(h), ws.data_ptr(), nb, st);
+                                fpm(h), ws.data_ptr(), nb, on.stream);
   });
   return rc ? PyLong_FromLong(rc) : THPVariable_Wrap(h);
   END_HANDLE_TH_ERRORS
@@ -238,12 +247,12 @@ PyObject* decode(PyObject*, PyObject* const* a, Py_ssize_t n) {
   if (!f32(*s) || !shape(*s, {B, p.D, p.M, 2})) return none();
   const Tensor y = empty(x->sizes(), *x, x->scalar_type());
   const auto dt = (res_dtype_t)code(*x);
-  void* st = stream(*x);
+  const OnDevice on(*x);
   const int rc = call([&] {
     return STEPS ? resonator_decode_steps(x->data_ptr(), dt, y.data_ptr(), dt, B, N, p.D, p.M, p.gamma, p.omega, p.amp,
-                                          p.phase, fpm(*s), st)
+                                          p.phase, fpm(*s), on.stream)
                  : resonator_decode_step(x->data_ptr(), dt, y.data_ptr(), dt, B, p.D, p.M, p.gamma, p.omega, p.amp,
-                                         p.phase, fpm(*s), st);
+                                         p.phase, fpm(*s), on.stream);
   });
   return rc ? PyLong_FromLong(rc) : THPVariable_Wrap(y);
   END_HANDLE_TH_ERRORS
@@ -258,10 +267,11 @@ PyObject* decode_steps_tm(PyObject*, PyObject* const* a, Py_ssize_t n) {
   if (!x || !s || !y || x->dim() != 3 || code(*x) < 0 || code(*y) < 0 || y->sizes() != x->sizes() ||
       !params(a + 1, &p) || p.D != x->size(2) || !f32(*s) || !shape(*s, {x->size(1), p.D, p.M, 2}))
     return none();
-  void* st = stream(*x);
+  const OnDevice on(*x);
   const int rc = call([&] {
     return resonator_decode_steps_tm(x->data_ptr(), (res_dtype_t)code(*x), y->data_ptr(), (res_dtype_t)code(*y),
-                                     x->size(1), x->size(0), p.D, p.M, p.gamma, p.omega, p.amp, p.phase, fpm(*s), st);
+                                     x->size(1), x->size(0), p.D, p.M, p.gamma, p.omega, p.amp, p.phase, fpm(*s),
+                                     on.stream);
   });
   if (rc) return PyLong_FromLong(rc);
   Py_RETURN_TRUE;
@@ -287,10 +297,10 @@ PyObject* grouped_linear(PyObject*, PyObject* const* a, Py_ssize_t n) {
   auto s = x->sizes().vec();
   s.back() = d_out;
   const Tensor y = empty(s, *x, x->scalar_type());
-  void* st = stream(*x);
+  const OnDevice on(*x);
   const int rc = call([&] {
     return resonator_grouped_linear(x->data_ptr(), W->data_ptr(), (res_dtype_t)code(*x), y.data_ptr(), N, d_in, d_out,
-                                    G, st);
+                                    G, on.stream);
   });
   return rc ? PyLong_FromLong(rc) : THPVariable_Wrap(y);
   END_HANDLE_TH_ERRORS
@@ -309,10 +319,10 @@ PyObject* grouped_linear2(PyObject*, PyObject* const* a, Py_ssize_t n) {
   auto s = x->sizes().vec();
   s.back() = d_out;
   const Tensor y0 = empty(s, *x, x->scalar_type()), y1 = empty(s, *x, x->scalar_type());
-  void* st = stream(*x);
+  const OnDevice on(*x);
   const int rc = call([&] {
     return resonator_grouped_linear2(x->data_ptr(), W0->data_ptr(), W1->data_ptr(), (res_dtype_t)code(*x),
-                                     y0.data_ptr(), y1.data_ptr(), N, d_in, d_out, G, st);
+                                     y0.data_ptr(), y1.data_ptr(), N, d_in, d_out, G, on.stream);
   });
   return rc ? PyLong_FromLong(rc) : pack({y0, y1});
   END_HANDLE_TH_ERRORS
@@ -348,10 +358,10 @@ PyObject* bwd_data_sum(PyObject*, PyObject* const* a, Py_ssize_t na) {
   auto s = d[0]->sizes().vec();
   s.back() = G * di;
   const Tensor dx = empty(s, *d[0], d[0]->scalar_type());
-  void* st = stream(*d[0]);
+  const OnDevice on(*d[0]);
   const int rc = call([&] {
     return resonator_grouped_linear_bwd_data_sum(n, dp, wp, (res_dtype_t)code(*d[0]), dx.data_ptr(),
-                                                 d[0]->numel() / d_out, G * di, d_out, G, 0, st);
+                                                 d[0]->numel() / d_out, G * di, d_out, G, 0, on.stream);
   });
   return rc ? PyLong_FromLong(rc) : THPVariable_Wrap(dx);
   END_HANDLE_TH_ERRORS
@@ -392,11 +402,11 @@ PyObject* bwd_weight_sum(PyObject*, PyObject* const* a, Py_ssize_t na) {
   const auto dt = (res_dtype_t)code(*x);
   const size_t nb = resonator_grouped_linear_bwd_weight_sum_workspace_bytes(n, m, N, d_in, d_out, G, dt);
   const Tensor ws = empty({(int64_t)std::max<size_t>(nb, 256)}, *x, at::kByte);
-  void* st = stream(*x);
+  const OnDevice on(*x);
   const int rc = call([&] {
     return resonator_grouped_linear_bwd_weight_sum(n, x->data_ptr(), dp, outs, dt, fpm(*w[0]),
                                                    m == 2 ? fpm(*w[1]) : nullptr, N, d_in, d_out, G, 0, ws.data_ptr(),
-                                                   (size_t)ws.numel(), st);
+                                                   (size_t)ws.numel(), on.stream);
   });
   if (rc) return PyLong_FromLong(rc);
   Py_RETURN_TRUE;
@@ -416,10 +426,10 @@ PyObject* bwd_weight(PyObject*, PyObject* const* a, Py_ssize_t n) {
   if (d_in < 1 || d_out < 1 || G < 1 || d_in % G || d_out % G || !shape(*w, {G, d_in / G, d_out / G})) return none();
   const int64_t N = dy->numel() / d_out;
   if (x->numel() != N * d_in) return none();
-  void* st = stream(*x);
+  const OnDevice on(*x);
   const int rc = call([&] {
     return resonator_grouped_linear_bwd_weight(x->data_ptr(), dy->data_ptr(), (res_dtype_t)code(*x), fpm(*w), N, d_in,
-                                               d_out, G, acc, st);
+                                               d_out, G, acc, on.stream);
   });
   if (rc) return PyLong_FromLong(rc);
   Py_RETURN_TRUE;
@@ -470,10 +480,10 @@ PyObject* epilogue_fwd(PyObject*, PyObject* const* a, Py_ssize_t n) {
   const Tensor *g = like(a[1], *y), *v = e.K ? like(a[2], *y) : nullptr;
   if (!g || (e.K && !v)) return none();
   const Tensor z = empty(y->sizes(), *y, y->scalar_type());
-  void* st = stream(*y);
+  const OnDevice on(*y);
   const int rc = call([&] {
     return resonator_epilogue_fwd(y->data_ptr(), g->data_ptr(), v ? v->data_ptr() : nullptr, (res_dtype_t)code(*y),
-                                  z.data_ptr(), e.B, e.L, e.H, e.D / e.H, e.K, e.Ct, e.lc, e.w, e.s, st);
+                                  z.data_ptr(), e.B, e.L, e.H, e.D / e.H, e.K, e.Ct, e.lc, e.w, e.s, on.stream);
   });
   return rc ? PyLong_FromLong(rc) : THPVariable_Wrap(z);
   END_HANDLE_TH_ERRORS
@@ -492,11 +502,11 @@ PyObject* epilogue_proj_fwd(PyObject*, PyObject* const* a, Py_ssize_t n) {
   if (a[9] != Py_None && !(z = like(a[9], *y))) return none();
   const int64_t d_out = e.H * W->size(2);
   const Tensor o = empty({e.B, e.L, d_out}, *y, y->scalar_type());
-  void* st = stream(*y);
+  const OnDevice on(*y);
   const int rc = call([&] {
     return resonator_epilogue_proj_fwd(y->data_ptr(), g->data_ptr(), v ? v->data_ptr() : nullptr, (res_dtype_t)code(*y),
                                        W->data_ptr(), o.data_ptr(), z ? z->data_ptr() : nullptr, e.B, e.L, e.H,
-                                       e.D / e.H, e.K, d_out, e.Ct, e.lc, e.w, e.s, st);
+                                       e.D / e.H, e.K, d_out, e.Ct, e.lc, e.w, e.s, on.stream);
   });
   return rc ? PyLong_FromLong(rc) : THPVariable_Wrap(o);
   END_HANDLE_TH_ERRORS
@@ -521,13 +531,13 @@ PyObject* epilogue_bwd(PyObject*, PyObject* const* a, Py_ssize_t n) {
   }
   const size_t nb = resonator_epilogue_workspace_bytes(e.B, e.L, e.H, e.D / e.H, e.K);
   const Tensor ws = empty({(int64_t)nb}, *y, at::kByte);
-  void* st = stream(*y);
+  const OnDevice on(*y);
   const int rc = call([&] {
     return resonator_epilogue_bwd(y->data_ptr(), g->data_ptr(), v ? v->data_ptr() : nullptr, dz->data_ptr(),
                                   (res_dtype_t)code(*y), dy.data_ptr(), dg.data_ptr(),
                                   e.K ? dv.data_ptr() : nullptr, e.B, e.L, e.H, e.D / e.H, e.K, e.Ct, e.lc, e.w, e.s,
                                   fpm(dCt), fpm(dl), e.K ? fpm(dw) : nullptr, e.K ? fpm(ds) : nullptr, ws.data_ptr(),
-                                  nb, st);
+                                  nb, on.stream);
   });
   return rc ? PyLong_FromLong(rc) : pack({dy, dg, dv, dCt, dl, dw, ds});
   END_HANDLE_TH_ERRORS

@@ -143,6 +143,27 @@ def test_outputs_that_are_too_small_are_refused(ops):
         ops.resonator_decode_step(x[:, 0].contiguous(), *prm, h, out=torch.empty(B, D))
 
 
+@pytest.mark.skipif(torch.cuda.device_count() < 2, reason="needs two GPUs")
+def test_calls_run_on_their_tensors_gpu(ops):
+    """Calls and replays on the second GPU while the first is current (their default
+    streams are both the null stream, which means the current device)."""
+    g = torch.Generator(device="cuda:0").manual_seed(4)
+    prm, x = _params(40, 6, g), torch.randn(3, 500, 40, device="cuda:0", generator=g)
+    h = torch.randn(3, 40, 6, 2, device="cuda:0", generator=g)
+    outs = []
+    for dev in ("cuda:0", "cuda:1"):
+        p, xd, hd = [t.to(dev) for t in prm], x.to(dev), h.to(dev)
+        graph = ops.DecodeGraph(*p, hd, 5, x_dtype=torch.float32)
+        torch.cuda.synchronize(dev)
+        with torch.cuda.device(0):
+            r = [ops.resonator_mix_fwd(xd, *p), ops.resonator_state_init(xd, *p),
+                 graph.replay(xd[:, :5].transpose(0, 1).contiguous()), hd]
+        torch.cuda.synchronize(dev)
+        outs.append([t.cpu() for t in r])
+    for a, b in zip(*outs):
+        assert torch.equal(a, b)
+
+
 def test_decode_replay_under_capture(ops):
     """A replay launches the graph's kernel itself; captured, it still is the graph's work."""
     g = torch.Generator(device="cuda").manual_seed(3)
