@@ -332,25 +332,28 @@ class DecodeGraph:
         cap = torch.cuda.Stream(dev)
         cap.wait_stream(cur)
         with torch.cuda.stream(cap), torch.cuda.graph(self.graph, stream=cap):
-            check(_lib.lib().resonator_decode_steps_tm(
-                _ptr(self.x), _code(self.x), _ptr(self.y), _code(self.y), B, steps, D, M, *map(_ptr, self.params),
-                _ptr(state), _stream(dev)))
+            self._launch()
         cur.wait_stream(cap)
 
     def replay(self, x=None):
         """Run the K steps on the current stream (after copying ``x`` [K, B, D] into
         the drive buffer when given); returns the output buffer ``y``.
 
-        The graph holds one kernel, so outside a capture that kernel is launched
-        itself: a graph launch costs about 10 us more of host time."""
+        The graph holds one kernel, so that kernel is launched itself (a graph
+        launch costs about 10 us more of host time); inside a capture the launch is
+        recorded like any other.  ``graph`` is there for callers that replay it."""
         if x is not None:
             self.x.copy_(x)
-        if torch.cuda.is_current_stream_capturing():
-            self.graph.replay()
-            return self.y
         if _done((_NATIVE or _native()).decode_steps_tm(self.x, *self.params, self.state, self.y)) is None:
-            self.graph.replay()
+            with torch.cuda.device(self.x.device):  # not plain tensors: the same launch
+                self._launch()
         return self.y
+
+    def _launch(self):
+        N, B, D = self.x.shape
+        check(_lib.lib().resonator_decode_steps_tm(
+            _ptr(self.x), _code(self.x), _ptr(self.y), _code(self.y), B, N, D, self.params[0].shape[1],
+            *map(_ptr, self.params), _ptr(self.state), _stream(self.x.device)))
 
 
 def resonator_quadratic_reference(x, gamma, omega, amp, phase):

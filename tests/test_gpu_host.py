@@ -164,18 +164,40 @@ def test_calls_run_on_their_tensors_gpu(ops):
         assert torch.equal(a, b)
 
 
-def test_decode_replay_under_capture(ops):
-    """A replay launches the graph's kernel itself; captured, it still is the graph's work."""
+@pytest.mark.parametrize("native", [True, False])
+def test_decode_replay_under_capture(monkeypatch, ops, native):
+    """A replay launches the graph's kernel itself: eagerly, recorded into a caller's
+    capture, and the same as the graph's own work, by either marshalling."""
     g = torch.Generator(device="cuda").manual_seed(3)
     prm, B, N, D, M = _params(24, 5, g), 3, 7, 24, 5
     x, s0 = torch.randn(N, B, D, device="cuda", generator=g), torch.randn(B, D, M, 2, device="cuda", generator=g)
     live, ref = s0.clone(), s0.clone()
     graph = ops.DecodeGraph(*prm, live, N, x_dtype=x.dtype)
+    if not native:
+        monkeypatch.setattr(ops, "_NATIVE", _Off())
+
+    def want():
+        return ops.resonator_decode_steps(x.transpose(0, 1).contiguous(), *prm, ref).transpose(0, 1)
+
     for _ in range(3):
         y = graph.replay(x)
-        want = ops.resonator_decode_steps(x.transpose(0, 1).contiguous(), *prm, ref)
+        w = want()
         torch.cuda.synchronize()
-        assert torch.equal(y, want.transpose(0, 1)) and torch.equal(live, ref)
+        assert torch.equal(y, w) and torch.equal(live, ref)
     graph.graph.replay()
-    want = ops.resonator_decode_steps(x.transpose(0, 1).contiguous(), *prm, ref)
-    assert torch.equal(graph.y, want.transpose(0, 1)) and torch.equal(live, ref)
+    assert torch.equal(graph.y, want()) and torch.equal(live, ref)
+    static = x.clone()
+    outer = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(outer):
+        y = graph.replay(static)
+        twice = y * 2
+    assert torch.equal(live, ref)  # recorded, not run
+    for i in range(4):
+        x = torch.randn(N, B, D, device="cuda", generator=g)
+        static.copy_(x)
+        outer.replay()
+        w = want()
+        torch.cuda.synchronize()
+        assert torch.equal(graph.y, w) and torch.equal(twice, w * 2) and torch.equal(live, ref)
+        _ = (x * i).sum().item()  # eager work between the replays
