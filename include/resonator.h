@@ -227,7 +227,7 @@ int resonator_decode_step_tab(const void* x_t, res_dtype_t x_dt, void* y_t, res_
 int resonator_decode_steps(const void* x, res_dtype_t x_dt, void* y, res_dtype_t y_dt, int64_t B, int64_t N,
                            int64_t D, int64_t M, const float* gamma, const float* omega, const float* amp,
                            const float* phase, float* state, void* stream);
-/* The same with time-major drives and outputs, x and y [N][B][D] (a block of tokens). */
+/* The same with time-major drives and outputs, x and y [N][B][D] (a block of tokens), for any B. */
 int resonator_decode_steps_tm(const void* x, res_dtype_t x_dt, void* y, res_dtype_t y_dt, int64_t B, int64_t N,
                               int64_t D, int64_t M, const float* gamma, const float* omega, const float* amp,
                               const float* phase, float* state, void* stream);

@@ -658,8 +658,8 @@ static int decode_steps_impl(const void* x, res_dtype_t x_dt, void* y, res_dtype
                              float* state, void* stream, bool time_major) {
   int rc = check_sizes(B, N, D, M, false);
   if (rc) return rc;
-  if (B > 4 * 65535LL) return fail(RES_ERR_UNSUPPORTED, "B must be <= %lld for this launch (got %lld)",
-                                   4 * 65535LL, (long long)B);
+  if (!time_major && B > 4 * 65535LL)
+    return fail(RES_ERR_UNSUPPORTED, "B must be <= %lld for this launch (got %lld)", 4 * 65535LL, (long long)B);
   if (!dtype_ok(x_dt) || !dtype_ok(y_dt)) return fail(RES_ERR_INVALID_ARG, "unknown dtype code");
   if (x_dt == RES_F32 && y_dt == RES_BF16)
     return fail(RES_ERR_UNSUPPORTED, "dtype pair f32 -> bf16 is not supported");

@@ -382,8 +382,9 @@ __global__ __launch_bounds__(DMW_CH* DMW_ROWS) void decode_steps_wide_kernel(
     const float* __restrict__ phase, float* __restrict__ state) {
   __shared__ float2 lhi[DMW_CH][MM], llo[DMW_CH][MM], cs[DMW_CH][MM];
   const int tid = threadIdx.x;
-  const int d0 = blockIdx.x * DMW_CH;
-  const int b0 = blockIdx.y * DMW_ROWS;
+  const unsigned nd = (unsigned)(D + DMW_CH - 1) / DMW_CH;  // blocks of a row group (a one-dimensional grid: any B)
+  const int d0 = (int)(blockIdx.x % nd) * DMW_CH;
+  const int b0 = (int)(blockIdx.x / nd) * DMW_ROWS;
   for (int t = tid; t < DMW_CH * M; t += blockDim.x) {
     const int dl = t / M, m = t % M, d = d0 + dl;
     float2 hi = make_float2(0.f, 0.f), lo = hi, c = hi;
@@ -452,7 +453,7 @@ hipError_t launch_decode_steps(int64_t B, int64_t N, int64_t D, int64_t M, const
                                const float* phase, float* state, hipStream_t st) {
   const int64_t sn = time_major ? B * D : D, sb = time_major ? D : N * D;
   if (B * D > DMW_MAX_PAIRS) {
-    const dim3 wgrid((unsigned)((D + DMW_CH - 1) / DMW_CH), (unsigned)((B + DMW_ROWS - 1) / DMW_ROWS));
+    const dim3 wgrid((unsigned)((D + DMW_CH - 1) / DMW_CH * ((B + DMW_ROWS - 1) / DMW_ROWS)));
     if (M <= 8)
       hipLaunchKernelGGL((decode_steps_wide_kernel<TX, TY, 8>), wgrid, dim3(DMW_CH * DMW_ROWS), 0, st,
                          reinterpret_cast<const TX*>(x), reinterpret_cast<TY*>(y), (int)B, N, (int)D, (int)M, sn, sb,

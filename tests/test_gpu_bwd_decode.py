@@ -244,6 +244,22 @@ def test_decode_steps_kernel_choice(B, D, M, N, act):
     assert torch.equal(yg, ye.transpose(0, 1)) and torch.equal(st3, st1)
 
 
+@pytest.mark.parametrize("B,D,M", [(262144, 1, 1), (300001, 2, 9)])
+def test_decode_graph_of_many_rows(B, D, M):
+    """More batch rows than a grid's second dimension holds in blocks of four:
+    bitwise the single steps."""
+    say(f"decode graph B={B} D={D} M={M}")
+    g = torch.Generator(device="cuda").manual_seed(B)
+    r = lambda *s: torch.randn(*s, device="cuda", generator=g)
+    pr = [r(D, M).abs() + 1e-3, r(D, M), r(D, M), r(D, M)]
+    x, st0 = r(3, B, D), r(B, D, M, 2)
+    st1, st2 = st0.clone(), st0.clone()
+    want = torch.stack([ops.resonator_decode_step(x[t], *pr, st1) for t in range(3)])
+    got = ops.DecodeGraph(*pr, st2, 3, x_dtype=torch.float32).replay(x)
+    torch.cuda.synchronize()
+    assert torch.equal(got, want) and torch.equal(st2, st1)
+
+
 def _oracle_rows(args):
     """Oracle recurrence over one group of batch rows (a worker thread's share)."""
     x, h0, prm = args
