@@ -266,17 +266,27 @@ RES_DECODE_TAB_INST(bf16_t, float)
 // batch of R steps ahead.  All exchange stays inside a wave (no barrier in the
 // step loop).
 //
-// A block is CH channels x DMS_ROWS batch rows (one wave per row).  The
+// A block is CH channels x DMS_ROWS batch rows (one wave per row).  The up to
 // DMS_XCD blocks of neighbouring channels that share the 128-byte lines of a
 // row's drives and outputs are 8 apart in the grid, which the dispatcher places
-// on one XCD (work-groups go round-robin over the 8 XCDs).
+// on one XCD (work-groups go round-robin over the 8 XCDs).  Narrow inputs have
+// smaller groups, so that no block starts only to end (B4096 D16: 10 us with
+// groups of 8, of which 2 had work).
 // ---------------------------------------------------------------------------
 constexpr int DMS_ROWS = 4;  // waves of a block
 constexpr int DMS_XCD = 8;
 
+// log2 of the blocks of a group, for a row of D channels in blocks of ch: a power of
+// two up to DMS_XCD (shifts in the kernel: divisions by it cost 0.6 us at B160 D256)
+inline int dms_group(int64_t D, int ch) {
+  int lx = 0;
+  while ((1 << lx) < DMS_XCD && (int64_t)ch << lx < D) ++lx;
+  return lx;
+}
+
 template <typename TX, typename TY, int R>
 __global__ __launch_bounds__(64 * DMS_ROWS) void decode_steps_kernel(
-    const TX* __restrict__ x, TY* __restrict__ y, int B, int64_t N, int D, int M, int64_t sn, int64_t sb,
+    const TX* __restrict__ x, TY* __restrict__ y, int B, int64_t N, int D, int M, int lx, int64_t sn, int64_t sb,
     const float* __restrict__ gamma, const float* __restrict__ omega, const float* __restrict__ amp,
     const float* __restrict__ phase, float* __restrict__ state) {
   constexpr int CH = 64 / R;         // channels of a block
@@ -287,13 +297,14 @@ __global__ __launch_bounds__(64 * DMS_ROWS) void decode_steps_kernel(
   __shared__ __align__(16) float2 hs[DMS_ROWS * CH * HGRP];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int m = lane % R, cl = lane / R;
-  // block -> (row block, channel block): member k of a group of DMS_XCD channel
+  // block -> (row block, channel block): member k of a group of 2^lx channel
   // blocks, groups over channels then rows
   const unsigned bid = blockIdx.x;
-  const int64_t grp = (int64_t)(bid / (8 * DMS_XCD)) * 8 + (bid & 7);
-  const int ngd = (D + CH * DMS_XCD - 1) / (CH * DMS_XCD);
-  const int d0 = ((int)(grp % ngd) * DMS_XCD + (int)((bid >> 3) % DMS_XCD)) * CH;
-  const int64_t b0 = grp / ngd * DMS_ROWS;
+  const unsigned grp = (bid >> (3 + lx)) * 8 + (bid & 7);
+  const unsigned ngd = (unsigned)(D + (CH << lx) - 1) >> ((R == 8 ? 3 : 2) + lx);
+  const unsigned gr = grp / ngd;
+  const int d0 = (int)(((grp - gr * ngd) << lx) + ((bid >> 3) & ((1u << lx) - 1))) * CH;
+  const int64_t b0 = (int64_t)gr * DMS_ROWS;
   if (d0 >= D || b0 >= B) return;  // the whole block
   const int64_t b = b0 + wave;
   const int d = d0 + cl;
@@ -369,22 +380,46 @@ __global__ __launch_bounds__(64 * DMS_ROWS) void decode_steps_kernel(
 // waves to fill the SIMDs it needs no exchange and is the faster one.
 constexpr int DMW_CH = 64;
 constexpr int DMW_ROWS = 4;
-// (b, d) pairs above which one thread per pair is faster (128 steps, M = 8: at
-// 16384 pairs 52 us against 17 with a lane per mode, at 65536 55 against 38, at
-// 131072 58 against 65, at 262144 92 against 125; M = 2: 35 against 36 at 65536,
-// 37 against 46 at 98304; M = 16: 99 against 68 and 105 against 132)
-constexpr int64_t DMW_MAX_PAIRS = 1 << 16;
+// Whether one thread per pair is the faster of the two.  Above 65536 pairs it is
+// (128 steps, M = 8: at 65536 pairs 55 us against 38 with a lane per mode, at
+// 131072 58 against 65, at 262144 92 against 125; M = 2: 37 against 46 at 98304).
+// Below, the times of both follow these fits (us; bf16, 16000 to 65536 pairs, M 1
+// to 16, 1 to 64 steps; within 10 % where the two are close).  A lane per mode:
+// the work is its waves' (kw thousand), idle lanes (M < R) among them.  A thread
+// per pair: the latency of M modes in turn, more where a narrow D leaves lanes
+// idle and so more than two thousand waves.  At 65536 pairs of 256 channels, a
+// lane per mode against a thread per pair: M = 1 one step 6.4, 4.4, 64 steps 21.0,
+// 17.9; M = 4 8 steps 7.5, 7.0, 64 steps 21.4, 22.6; M = 8 one step 7.2, 8.3; M = 9
+// one step 14.0, 10.3.
+static bool steps_wide(int64_t B, int64_t D, int64_t M, int64_t N) {
+  if (B * D > (1 << 16)) return true;
+  const int R = M <= 8 ? 8 : 16, ch = 64 / R;
+  const bool bank = M > 8;
+  const double m = (double)M, n = (double)(N - 1), kw = (double)((D + ch - 1) / ch * B) / 1024;
+  const double lane = bank ? 2.6 + 0.72 * kw + n * kw * (N <= 16 ? 0.018 : 0.0255)
+                           : 3.8 + 0.22 * kw + (kw > 7 ? 0.8 : 0.0) + n * (kw > 3.3 ? 0.027 * kw : 0.09);
+  const double ww = (double)((D + DMW_CH - 1) / DMW_CH * B) / 1024, over = ww > 2 ? ww - 2 : 0;
+  const double base = D < DMW_CH ? 4.2 + 0.36 * m : M <= 4 ? 4.0 + 0.3 * m : bank ? 5.0 + 0.5 * m : 4.0 + 0.45 * m;
+  const double step = bank ? (0.14 + 0.045 * m) * (1 + 0.47 * over) : (0.18 + 0.025 * m) * (1 + 0.21 * over);
+  return base + over * (bank ? 2.6 : 0.6) + n * step < lane;
+}
 
-template <typename TX, typename TY, int MM>
+// ROWS: batch-major strides formed here from N and D (16 modes, 98304 pairs, 64
+// steps: 61 us against 64 with the given ones; 8 modes the given ones: 22.0 against
+// 23.0 at M = 3).
+template <typename TX, typename TY, int MM, bool ROWS>
 __global__ __launch_bounds__(DMW_CH* DMW_ROWS) void decode_steps_wide_kernel(
     const TX* __restrict__ x, TY* __restrict__ y, int B, int64_t N, int D, int M, int64_t sn, int64_t sb,
     const float* __restrict__ gamma, const float* __restrict__ omega, const float* __restrict__ amp,
     const float* __restrict__ phase, float* __restrict__ state) {
   __shared__ float2 lhi[DMW_CH][MM], llo[DMW_CH][MM], cs[DMW_CH][MM];
   const int tid = threadIdx.x;
-  const unsigned nd = (unsigned)(D + DMW_CH - 1) / DMW_CH;  // blocks of a row group (a one-dimensional grid: any B)
-  const int d0 = (int)(blockIdx.x % nd) * DMW_CH;
-  const int b0 = (int)(blockIdx.x / nd) * DMW_ROWS;
+  const int d0 = blockIdx.x * DMW_CH;
+  const int b0 = (int)(blockIdx.z * gridDim.y + blockIdx.y) * DMW_ROWS;  // over two dimensions: any B
+  if (ROWS) {
+    sn = D;
+    sb = N * D;
+  }
   for (int t = tid; t < DMW_CH * M; t += blockDim.x) {
     const int dl = t / M, m = t % M, d = d0 + dl;
     float2 hi = make_float2(0.f, 0.f), lo = hi, c = hi;
@@ -452,28 +487,35 @@ hipError_t launch_decode_steps(int64_t B, int64_t N, int64_t D, int64_t M, const
                                const float* gamma, const float* omega, const float* amp,
                                const float* phase, float* state, hipStream_t st) {
   const int64_t sn = time_major ? B * D : D, sb = time_major ? D : N * D;
-  if (B * D > DMW_MAX_PAIRS) {
-    const dim3 wgrid((unsigned)((D + DMW_CH - 1) / DMW_CH * ((B + DMW_ROWS - 1) / DMW_ROWS)));
-    if (M <= 8)
-      hipLaunchKernelGGL((decode_steps_wide_kernel<TX, TY, 8>), wgrid, dim3(DMW_CH * DMW_ROWS), 0, st,
-                         reinterpret_cast<const TX*>(x), reinterpret_cast<TY*>(y), (int)B, N, (int)D, (int)M, sn, sb,
-                         gamma, omega, amp, phase, state);
-    else
-      hipLaunchKernelGGL((decode_steps_wide_kernel<TX, TY, RES_M_MAX_DEV>), wgrid, dim3(DMW_CH * DMW_ROWS), 0, st,
-                         reinterpret_cast<const TX*>(x), reinterpret_cast<TY*>(y), (int)B, N, (int)D, (int)M, sn, sb,
-                         gamma, omega, amp, phase, state);
+  // One step of many pairs with a wide bank: the single-step kernel, whose states
+  // load 16 bytes at a time or stream through one mode at a time (M = 8, 1048576
+  // pairs: 38 us against 49, M = 16 75 against 129; M <= 2 is slower there, 18
+  // against 16, and M = 6 38 against 35)
+  if (N == 1 && M >= 8 && B * D > (1 << 16) && B <= DEC_ROWS * 65535LL)
+    return launch_decode<TX, TY>(B, D, M, x, y, gamma, omega, amp, phase, state, st);
+  if (steps_wide(B, D, M, N)) {
+    const int64_t nb = (B + DMW_ROWS - 1) / DMW_ROWS, gy = nb < 65535 ? nb : 65535;
+    const dim3 wgrid((unsigned)((D + DMW_CH - 1) / DMW_CH), (unsigned)gy, (unsigned)((nb + gy - 1) / gy));
+    const auto kernel = M <= 8       ? decode_steps_wide_kernel<TX, TY, 8, false>
+                        : time_major ? decode_steps_wide_kernel<TX, TY, RES_M_MAX_DEV, false>
+                                     : decode_steps_wide_kernel<TX, TY, RES_M_MAX_DEV, true>;
+    hipLaunchKernelGGL(kernel, wgrid, dim3(DMW_CH * DMW_ROWS), 0, st, reinterpret_cast<const TX*>(x),
+                       reinterpret_cast<TY*>(y), (int)B, N, (int)D, (int)M, sn, sb, gamma, omega, amp, phase, state);
     return hipGetLastError();
   }
   const int R = M <= 8 ? 8 : 16;
-  const int64_t gch = 64 / R * DMS_XCD;  // channels of a group of blocks
+  const int lx = dms_group(D, 64 / R);
+  const int64_t gch = (int64_t)(64 / R) << lx;  // channels of a group of blocks
   const int64_t groups = (D + gch - 1) / gch * ((B + DMS_ROWS - 1) / DMS_ROWS);
-  const dim3 grid((unsigned)((groups + 7) / 8 * 8 * DMS_XCD)), block(64 * DMS_ROWS);
+  const dim3 grid((unsigned)((groups + 7) / 8 * 8 << lx)), block(64 * DMS_ROWS);
   if (R == 8)
     hipLaunchKernelGGL((decode_steps_kernel<TX, TY, 8>), grid, block, 0, st, reinterpret_cast<const TX*>(x),
-                       reinterpret_cast<TY*>(y), (int)B, N, (int)D, (int)M, sn, sb, gamma, omega, amp, phase, state);
+                       reinterpret_cast<TY*>(y), (int)B, N, (int)D, (int)M, lx, sn, sb, gamma, omega, amp, phase,
+                       state);
   else
     hipLaunchKernelGGL((decode_steps_kernel<TX, TY, 16>), grid, block, 0, st, reinterpret_cast<const TX*>(x),
-                       reinterpret_cast<TY*>(y), (int)B, N, (int)D, (int)M, sn, sb, gamma, omega, amp, phase, state);
+                       reinterpret_cast<TY*>(y), (int)B, N, (int)D, (int)M, lx, sn, sb, gamma, omega, amp, phase,
+                       state);
   return hipGetLastError();
 }
 

@@ -244,6 +244,16 @@ def test_decode_steps_kernel_choice(B, D, M, N, act):
     assert torch.equal(yg, ye.transpose(0, 1)) and torch.equal(st3, st1)
 
 
+@pytest.mark.parametrize("B,D,M,N,act", [(512, 256, 8, 1, "bf16"), (1024, 65, 16, 1, "f32"), (1030, 64, 1, 2, "bf16"),
+                                         (4096, 16, 4, 3, "bf16"), (4096, 16, 8, 33, "f32"), (2000, 16, 10, 5, "bf16"),
+                                         (700, 9, 3, 11, "f32"), (129, 500, 12, 20, "bf16")])
+def test_decode_steps_kernel_rule(B, D, M, N, act):
+    """Both sides of the rule between a lane per mode and a thread per pair, narrow
+    inputs (small groups of channel blocks) and one step of many pairs: bitwise N
+    single steps."""
+    test_decode_steps_kernel_choice(B, D, M, N, act)
+
+
 @pytest.mark.parametrize("B,D,M", [(262144, 1, 1), (300001, 2, 9)])
 def test_decode_graph_of_many_rows(B, D, M):
     """More batch rows than a grid's second dimension holds in blocks of four:
