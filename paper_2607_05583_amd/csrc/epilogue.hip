@@ -783,14 +783,41 @@ static unsigned epi_grid(int64_t items) {
   return (unsigned)(g < 8192 ? (g > 0 ? g : 1) : 8192);
 }
 
+// Tile kernel of the backward; *nparts: the partial rows it wrote, one per
+// work-group (cap: what the workspace holds).  Work-groups loop over chunks, as
+// many of them as chunks and as the device runs at once: a work-group beyond those
+// starts when another ends and its parameter sums and their exchange come on top.
+// Kernels by what their registers let a compute unit run (time in us on 1, 2 and 3
+// work-groups per compute unit): float32, CPT 2, HM 8 (three) B4 L8192 H8 dh32 K4
+// 111, 71, 62, and 77 on four; bf16, CPT 4, HM 8 (two) 73, 55, 65; CPT 1 (one) bf16
+// B4 L8192 H3 dh7 K4 31, 51, 57; HM 32 (one) float32 B8 L8192 H16 dh16 K2 293, 299,
+// 304.  Chunks get shorter, down to one row per thread, while there are fewer of
+// them than work-groups that run: a work-group's time is mostly fixed ([1, 777, 128]
+// float32: 29.5 us on 13 work-groups of 64 rows, 11 on 195 of 4).
 template <typename T, int CPT, int HM>
-static void tile_bwd(const void* y, const void* gate, const void* v, const void* dz, void* dy, void* dgate, void* dv,
-                     int64_t B, int64_t L, int H, int dh, int K, int R, const float* Ct, float lambda_c,
-                     const float* w, const float* s, float* part, unsigned nparts, hipStream_t st) {
-  hipLaunchKernelGGL((epi_bwd_tile_kernel<T, CPT, HM>), dim3(nparts), dim3(256),
+static hipError_t tile_bwd(const void* y, const void* gate, const void* v, const void* dz, void* dy, void* dgate,
+                           void* dv, int64_t B, int64_t L, int H, int dh, int K, const float* Ct, float lambda_c,
+                           const float* w, const float* s, float* part, int64_t cap, int64_t* nparts,
+                           hipStream_t st) {
+  int R = epi_tile_rows(true, H * dh, H, K, CPT, sizeof(T));
+  int dev = 0, ncu = 0, per = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e == hipSuccess) e = hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
+  if (e == hipSuccess)
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, epi_bwd_tile_kernel<T, CPT, HM>, 256,
+                                                     epi_tile_lds(true, H * dh, H, K, CPT, sizeof(T), R));
+  if (e != hipSuccess) return e;
+  const int64_t run = (int64_t)(per < 1 ? 1 : per) * (ncu < 1 ? 256 : ncu);
+  const int RP = tile_geo(H * dh, CPT).RP;
+  while (R - RP >= RP && B * ((L + R - 1) / R) < run) R -= RP;
+  const int64_t nch = B * ((L + R - 1) / R);
+  *nparts = nch < run ? nch : run;
+  if (*nparts > cap) *nparts = cap;
+  hipLaunchKernelGGL((epi_bwd_tile_kernel<T, CPT, HM>), dim3((unsigned)*nparts), dim3(256),
                      epi_tile_lds(true, H * dh, H, K, CPT, sizeof(T), R), st, (const T*)y, (const T*)gate,
                      (const T*)v, (const T*)dz, (T*)dy, (T*)dgate, (T*)dv, B, L, H, dh, K, R, Ct, lambda_c, w, s,
                      part);
+  return hipGetLastError();
 }
 
 template <typename T, int CPT, int HM, bool WL>
@@ -830,29 +857,18 @@ hipError_t launch_epi_bwd(const void* y, const void* gate, const void* v, const 
   hipError_t e;
   const int cpt = epi_tile_cpt<T>(vec, H * dh, H, K, true);
   if (cpt) {
-    // one partial row per block; blocks loop over chunks, as many blocks as chunks
-    // up to two per compute unit (the bf16 kernel's 235 registers let two run:
-    // B4 L8192 bf16 takes 52 us on 512 blocks, 63 on 1024) and up to what the
-    // workspace holds.  Chunks get shorter, down to one row per thread, while there
-    // are fewer of them than blocks: a block's time is mostly fixed (13 blocks, one
-    // per 64 rows, for [1, 777, 128] float32: 29.5 us; 195 of 4 rows: 11).
-    int R = epi_tile_rows(true, H * dh, H, K, cpt, sizeof(T));
-    const int RP = tile_geo(H * dh, cpt).RP;
-    while (R - RP >= RP && B * ((L + R - 1) / R) < 512) R -= RP;
-    const int64_t nch = B * ((L + R - 1) / R);
-    const int64_t least = epi_part_rows_min(B, L) < EPI_PARTS ? epi_part_rows_min(B, L) : EPI_PARTS;
-    const int64_t cap = epi_bytes_of_rows(EPI_PARTS, H, dh, K) <= ws_bytes || nch <= least ? EPI_PARTS : least;
-    nparts = nch < cap ? nch : cap;
-    const unsigned np = (unsigned)nparts;
+    const int64_t cap = epi_bytes_of_rows(EPI_PARTS, H, dh, K) <= ws_bytes || nblk > EPI_PARTS ? EPI_PARTS : nblk;
     if (cpt == WIDE && H <= 8)
-      tile_bwd<T, WIDE, 8>(y, gate, v, dz, dy, dgate, dv, B, L, H, dh, K, R, Ct, lambda_c, w, s, part, np, st);
+      e = tile_bwd<T, WIDE, 8>(y, gate, v, dz, dy, dgate, dv, B, L, H, dh, K, Ct, lambda_c, w, s, part, cap, &nparts, st);
     else if (cpt == WIDE)
-      tile_bwd<T, WIDE, EPI_H_MAX>(y, gate, v, dz, dy, dgate, dv, B, L, H, dh, K, R, Ct, lambda_c, w, s, part, np, st);
+      e = tile_bwd<T, WIDE, EPI_H_MAX>(y, gate, v, dz, dy, dgate, dv, B, L, H, dh, K, Ct, lambda_c, w, s, part, cap,
+                                       &nparts, st);
     else if (H <= 8)
-      tile_bwd<T, 1, 8>(y, gate, v, dz, dy, dgate, dv, B, L, H, dh, K, R, Ct, lambda_c, w, s, part, np, st);
+      e = tile_bwd<T, 1, 8>(y, gate, v, dz, dy, dgate, dv, B, L, H, dh, K, Ct, lambda_c, w, s, part, cap, &nparts, st);
     else
-      tile_bwd<T, 1, EPI_H_MAX>(y, gate, v, dz, dy, dgate, dv, B, L, H, dh, K, R, Ct, lambda_c, w, s, part, np, st);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
+      e = tile_bwd<T, 1, EPI_H_MAX>(y, gate, v, dz, dy, dgate, dv, B, L, H, dh, K, Ct, lambda_c, w, s, part, cap,
+                                    &nparts, st);
+    if (e != hipSuccess) return e;
   } else {
     const int64_t rows = B * L;
     const int ov = vec >= 2 ? 2 : 1;

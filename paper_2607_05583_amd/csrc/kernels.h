@@ -16,8 +16,8 @@ constexpr int EPI_ROWS = 64;    // rows per block partial
 // Workspace of the epilogue backward: rows of block partials (one per work-group
 // of the parameter sums), then H*H float64 terms.  The generic kernels write one
 // row per EPI_ROWS rows of activations; the tile kernel as many as it has
-// work-groups (at most EPI_PARTS), so that short inputs still fill the device.
-constexpr int64_t EPI_PARTS = 512;
+// work-groups (at most EPI_PARTS: three on each of 256 compute units).
+constexpr int64_t EPI_PARTS = 768;
 inline int64_t epi_part_cols(int64_t H, int64_t dh, int64_t K) { return H * H + H * dh + H * dh * K; }
 inline int64_t epi_part_rows_min(int64_t B, int64_t L) { return B * ((L + EPI_ROWS - 1) / EPI_ROWS); }
 inline size_t epi_bytes_of_rows(int64_t rows, int64_t H, int64_t dh, int64_t K) {

@@ -206,3 +206,12 @@ def test_epilogue_bwd_many_blocks():
     say("  errs " + " ".join(f"{k}={v:.2e}" for k, v in errs.items()))
     for n, e in errs.items():
         assert e <= (1.5e-2 if n in ("dy", "dgate", "dv") else 1e-3), n
+
+
+# More chunks than the work-groups a kernel instance runs at once (one, two or
+# three per compute unit): single channels, 32 heads' accumulators, float32 pairs.
+@pytest.mark.parametrize("case", [(4, 4000, 3, 7, 4, "bf16"), (1, 8000, 16, 16, 2, "f32"), (3, 6000, 8, 16, 3, "f32"),
+                                  (1, 1001, 20, 3, 2, "bf16")],
+                         ids=lambda c: "B{}_L{}_H{}_dh{}_K{}_{}".format(*c))
+def test_epilogue_bwd_more_chunks_than_blocks(case):
+    test_epilogue_bwd_parity(case)
