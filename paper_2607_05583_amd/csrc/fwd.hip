@@ -931,9 +931,9 @@ __device__ __forceinline__ void stage_operands(const char* st, int k, int i, int
 // exchanging rows of 16 lanes between the four results (two 32-lane and two
 // 16-lane swaps per register) gives lane (c, q) of R[j] the chunks 4j .. 4j+3
 // of channel q.
-template <typename TX>
-__device__ __forceinline__ void chunk_states(const typename FPath<TX>::XOp (&xv)[4],
-                                             const typename FPath<TX>::AOp (&vop)[4], float (&S)[16]) {
+template <typename TX, typename VOp>
+__device__ __forceinline__ void chunk_states(const typename FPath<TX>::XOp (&xv)[4], const VOp (&vop)[4],
+                                             float (&S)[16]) {
   const f4 zero = {0.f, 0.f, 0.f, 0.f};
   f4 R[4];
 #pragma unroll
@@ -1361,7 +1361,9 @@ __global__ __launch_bounds__(StreamGeo<TX>::NT, 1) void fwd_stream_kernel(Stream
 // of 8 steps), and the carried state in float64, E <- lambda^256 E + lambda^128
 // A_0 + A_1.  One segment per chain when the chains fill the device; else the
 // segments' end states are folded by state_fold_kernel.  Nothing but x is read
-// per tile: bound by HBM (B64 L1024 D256 bf16: 33.5 MB).  One kernel that builds
+// per tile: bound by HBM (B64 L1024 D256 bf16: 33.5 MB).  V keeps its float32
+// bits for bf16 drives too (three bf16 parts): with two, 17 bits, the state of that
+// case was 1.9e-6 off and is 1.5e-7, at 2 to 4 % more time.  One kernel that builds
 // its own tables took the place of tables, tile aggregates and carry fold (28 us
 // there).
 // ---------------------------------------------------------------------------
@@ -1444,7 +1446,7 @@ __global__ __launch_bounds__(StreamGeo<TX>::NT, 1) void state_kernel(StreamArgs 
   float2* stage = reinterpret_cast<float2*>(buf(1));
   const float sgn = (ln & 1) ? 1.f : -1.f;
   const int kmode = (cb + lq) * 8 + (ln >> 1);  // (channel, mode) of scan lane (component ln, channel lq)
-  typename PT::AOp vop[MG][4];
+  typename PT::AFull vop[MG][4];
   float2 mu[MG];
 #pragma unroll
   for (int g = 0; g < MG; ++g) {
@@ -1463,7 +1465,7 @@ __global__ __launch_bounds__(StreamGeo<TX>::NT, 1) void state_kernel(StreamArgs 
         const float2 z = pw[15 - 4 * lq - r];
         v[r] = (ln & 1) ? z.y : z.x;
       }
-      vop[g][c] = PT::split_a(v);
+      vop[g][c] = PT::full_a(v);
     }
     const float2 z = stage[kmode * PP + 16];
     mu[g] = make_float2(z.x, sgn * z.y);

@@ -65,8 +65,9 @@ template <> struct FPath<float> {
     const f4 r = {__uint_as_float(u.x), __uint_as_float(u.y), __uint_as_float(u.z), __uint_as_float(u.w)};
     return r;
   }
-  // the operand of a lane's four float32 entries
-  __device__ static __forceinline__ AOp split_a(const float (&v)[4]) { return f4{v[0], v[1], v[2], v[3]}; }
+  // the operand of a lane's four float32 entries with all their bits
+  typedef AOp AFull;
+  __device__ static __forceinline__ AFull full_a(const float (&v)[4]) { return f4{v[0], v[1], v[2], v[3]}; }
   __device__ static __forceinline__ f4 mma(const AOp& a, const XOp& x, f4 c) { return mma_f32(a, x, c); }
   // (A x)^T: lane (i, q) gets columns 4q .. 4q+3 of row i of A x
   __device__ static __forceinline__ f4 mma_t(const XOp& x, const AOp& a, f4 c) { return mma_f32(x, a, c); }
@@ -115,16 +116,33 @@ template <> struct FPath<bf16_t> {
     a.lo = __builtin_bit_cast(s4, make_uint2(u.z, u.w));
     return a;
   }
-  // the operand of a lane's four float32 entries, split into bf16 halves
-  __device__ static __forceinline__ AOp split_a(const float (&v)[4]) {
-    typedef __bf16 b4 __attribute__((ext_vector_type(4)));
-    b4 hi, lo;
+  // the operand of a lane's four float32 entries with all their bits, in three
+  // bf16 parts of 8 bits each (remainders as in split_h)
+  struct AFull {
+    s4 hi, mid, lo;
+  };
+  __device__ static __forceinline__ AFull full_a(const float (&v)[4]) {
+    typedef __bf16 b2 __attribute__((ext_vector_type(2)));
+    uint32_t u10 = 0x0000BF80u, u01 = 0xBF800000u;
+    asm("" : "+s"(u10), "+s"(u01));
+    const b2 m10 = __builtin_bit_cast(b2, u10), m01 = __builtin_bit_cast(b2, u01);
+    uint32_t part[3][2];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      hi[i] = (__bf16)v[i];
-      lo[i] = (__bf16)(v[i] - (float)hi[i]);
+    for (int i = 0; i < 2; ++i) {
+      float r0 = v[2 * i], r1 = v[2 * i + 1];
+#pragma unroll
+      for (int j = 0; j < 3; ++j) {
+        const b2 h = {(__bf16)r0, (__bf16)r1};
+        part[j][i] = __builtin_bit_cast(uint32_t, h);
+        if (j < 2) {
+          r0 = __builtin_amdgcn_fdot2_f32_bf16(h, m10, r0, false);
+          r1 = __builtin_amdgcn_fdot2_f32_bf16(h, m01, r1, false);
+        }
+      }
     }
-    return AOp{__builtin_bit_cast(s4, hi), __builtin_bit_cast(s4, lo)};
+    return AFull{__builtin_bit_cast(s4, make_uint2(part[0][0], part[0][1])),
+                 __builtin_bit_cast(s4, make_uint2(part[1][0], part[1][1])),
+                 __builtin_bit_cast(s4, make_uint2(part[2][0], part[2][1]))};
   }
   __device__ static __forceinline__ f4 mma(const AOp& a, const XOp& x, f4 c) {
     c = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a.hi, x, c, 0, 0, 0);
@@ -133,6 +151,11 @@ template <> struct FPath<bf16_t> {
   // (A x)^T: lane (i, q) gets columns 4q .. 4q+3 of row i of A x
   __device__ static __forceinline__ f4 mma_t(const XOp& x, const AOp& a, f4 c) {
     c = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(x, a.hi, c, 0, 0, 0);
+    return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(x, a.lo, c, 0, 0, 0);
+  }
+  __device__ static __forceinline__ f4 mma_t(const XOp& x, const AFull& a, f4 c) {
+    c = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(x, a.hi, c, 0, 0, 0);
+    c = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(x, a.mid, c, 0, 0, 0);
     return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(x, a.lo, c, 0, 0, 0);
   }
   // y += U H for float32 states H (lane (n, q): components 4q .. 4q+3 of chunk n):

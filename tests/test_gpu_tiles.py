@@ -48,3 +48,21 @@ def test_forward_partial_tiles(B, L, D, M, act, out):
     yr, hr = O.mix_recurrence(act64(prob["x"], act), *params_np(prob), h0=prob["h0"])
     assert rel_err(host(y), yr) <= tol(act, out)
     assert rel_err(host(h), hr) <= (1e-4 if act == "f32" else 2e-2)
+
+
+@pytest.mark.parametrize("L,D,M", [(16, 64, 8), (16, 24, 16), (11, 65, 3), (300, 64, 8), (4096, 40, 16)])
+@pytest.mark.parametrize("act", ["f32", "bf16"])
+def test_prompt_state_keeps_float32_bits(L, D, M, act):
+    """Drives only in the last 16 steps (one chunk, nothing to damp an error).  Powers
+    rounded once to float32 and float32 sums of 16 terms: each rounding is at most
+    2^-24 of the sum of the terms' magnitudes, 17 of them (two-part bf16 powers are
+    2^-17 off)."""
+    from paper_2607_05583_amd import ops
+    say(f"prompt state bits L={L} D={D} M={M} {act}")
+    prob = _prob(L + D, 2, L, D, M, act)
+    prob["x"][:, :max(L - 16, 0)] = 0
+    st = host(ops.resonator_state_init(dev_act(prob["x"], act), *params_dev(prob)))
+    x, p = act64(prob["x"], act), params_np(prob)
+    ref = O.state_init(x, *p)
+    lim = O.state_init(np.abs(x), p[0], np.zeros_like(p[1]), *p[2:])[..., :1]  # sum of |lambda|^k |x|
+    assert np.all(np.abs(st - ref) <= 17 * 2.0 ** -24 * lim + 1e-30)
