@@ -406,17 +406,25 @@ __global__ __launch_bounds__(NTHREADS, MG == 1 ? 4 : 2) void fwd_agg_kernel(FwdA
 
 // ---------------------------------------------------------------------------
 // Carry kernel: for every (row, channel, mode) the states entering each tile.
-// The tiles of a row are cut into at most 64 segments of 4 * 2^k tiles;
+// The tiles of a row are cut into at most 64 segments of BLK * 2^k tiles;
 // thread (pair, segment) folds its segment's aggregates from zero (float64), the
 // segment entry states follow from the segment aggregates in order, and each
 // thread replays its segment to write the entry states of both tile halves
 // (c, mu^8 c + A_0).  The last
 // segment also writes the state at t = L-1: lambda^last_len c_last + alast.
-// The fold order is fixed by P alone, so the result is bitwise reproducible.
+// The fold order is fixed by the sizes alone, so the result is bitwise reproducible.
 // ---------------------------------------------------------------------------
 constexpr int CARRY_SEG_MAX = 64;  // segments per row (threads per pair)
-constexpr int CARRY_BLOCK = 4;     // records loaded together (16: 10.0 us at B4 L8192 D256 M16 bf16, 8: 8.4, 4: 7.4)
+// Records a thread loads together, and the least segment.  Rows of up to 128 tiles
+// are bound by the number of threads: 4 (B4 L8192 D256 M16 bf16, 32 tiles a row:
+// the kernel 10.0 us with 16, 8.4 with 8, 7.4 with 4).  Longer ones by the loads in
+// flight: 16, when that still leaves a wave for every SIMD or the segments are that
+// long anyway (the whole forward with M = 16 bf16, 16 against 4: B4 L131072 D128
+// 283 and 308 us, B8 L65536 D64 145 and 150, B1 L262144 D256 292 and 306; but B8
+// L32768 D64 89 and 86, and with fewer threads B1 L65536 D64 41.4 and 39.6).
+constexpr int CARRY_BLOCK = 4, CARRY_BLOCK_LONG = 16;
 
+template <int BLK>
 __global__ __launch_bounds__(256) void fwd_carry_kernel(FwdArgs a, int seg_len, int nseg, int nsegp,
                                                         int pairs_per_tile, int cpw, int pairs_w) {
   __shared__ double2 sg[256];  // segment aggregates, then entry states
@@ -444,24 +452,24 @@ __global__ __launch_bounds__(256) void fwd_carry_kernel(FwdArgs a, int seg_len, 
     mu8 = cc.mu8;
   }
   const int64_t p0 = (int64_t)seg * seg_len;
-  const int nsub = seg_len / CARRY_BLOCK;
+  const int nsub = seg_len / BLK;
   // records of tile p0 + i of this (row, pair): base[i * stride]
   const size_t stride = (size_t)nchains * pairs_per_tile;
   const float4* base = agg + (size_t)(p0 * nchains + chain) * pairs_per_tile + q;
   float4* cbase = car + (size_t)(p0 * nchains + chain) * pairs_per_tile + q;
   const int64_t nloc = valid ? (a.P - p0 < seg_len ? a.P - p0 : seg_len) : 0;  // tiles of this segment
-  float4 rec[CARRY_BLOCK];
+  float4 rec[BLK];
   // pass 1: the segment's end state from zero over its tiles before the row's last
   double2 acc = make_double2(0.0, 0.0);
   for (int sb = 0; sb < nsub; ++sb) {
 #pragma unroll
-    for (int i = 0; i < CARRY_BLOCK; ++i) {
-      const int64_t li = (int64_t)sb * CARRY_BLOCK + i;
+    for (int i = 0; i < BLK; ++i) {
+      const int64_t li = (int64_t)sb * BLK + i;
       rec[i] = li < nloc ? base[li * stride] : make_float4(0.f, 0.f, 0.f, 0.f);
     }
 #pragma unroll
-    for (int i = 0; i < CARRY_BLOCK; ++i)
-      if (p0 + (int64_t)sb * CARRY_BLOCK + i < a.P - 1)
+    for (int i = 0; i < BLK; ++i)
+      if (p0 + (int64_t)sb * BLK + i < a.P - 1)
         acc = zfma(lamT, acc, zfma(mu8, make_double2(rec[i].x, rec[i].y), make_double2(rec[i].z, rec[i].w)));
   }
   sg[tid] = acc;
@@ -484,14 +492,14 @@ __global__ __launch_bounds__(256) void fwd_carry_kernel(FwdArgs a, int seg_len, 
   for (int sb = 0; sb < nsub; ++sb) {
     if (nsub > 1) {  // a single block is still in registers
 #pragma unroll
-      for (int i = 0; i < CARRY_BLOCK; ++i) {
-        const int64_t li = (int64_t)sb * CARRY_BLOCK + i;
+      for (int i = 0; i < BLK; ++i) {
+        const int64_t li = (int64_t)sb * BLK + i;
         rec[i] = li < nloc ? base[li * stride] : make_float4(0.f, 0.f, 0.f, 0.f);
       }
     }
 #pragma unroll
-    for (int i = 0; i < CARRY_BLOCK; ++i) {
-      const int64_t li = (int64_t)sb * CARRY_BLOCK + i;
+    for (int i = 0; i < BLK; ++i) {
+      const int64_t li = (int64_t)sb * BLK + i;
       if (li < nloc) {
         const double2 A0 = make_double2(rec[i].x, rec[i].y), A1 = make_double2(rec[i].z, rec[i].w);
         const double2 half = zfma(mu8, cst, A0);
@@ -1637,19 +1645,27 @@ template hipError_t launch_fwd_agg<bf16_t>(const Geometry&, const FwdArgs&, hipS
                                            hipEvent_t);
 
 hipError_t launch_fwd_carry(const Geometry& g, const FwdArgs& a, hipStream_t st) {
-  // segments: at most CARRY_SEG_MAX per row, CARRY_BLOCK * 2^k tiles each
-  int seg_len = CARRY_BLOCK;
+  const int pairs_per_tile = g.DW * g.Mp;
+  const int64_t npairs = g.B * g.NB * (int64_t)pairs_per_tile;
+  const bool blk16 = g.P > CARRY_BLOCK_LONG / 2 * CARRY_SEG_MAX ||
+                     (g.P > 128 && npairs * ((g.P + CARRY_BLOCK_LONG - 1) / CARRY_BLOCK_LONG) >= 65536);
+  const int blk = blk16 ? CARRY_BLOCK_LONG : CARRY_BLOCK;
+  // segments: at most CARRY_SEG_MAX per row, blk * 2^k tiles each
+  int seg_len = blk;
   while ((g.P + seg_len - 1) / seg_len > CARRY_SEG_MAX) seg_len *= 2;
   const int nseg = (int)((g.P + seg_len - 1) / seg_len);
   int nsegp = 1;
   while (nsegp < nseg) nsegp *= 2;
   const int pw = 256 / nsegp;
-  const int pairs_per_tile = g.DW * g.Mp;
-  const int64_t npairs = g.B * g.NB * (int64_t)pairs_per_tile;
   const int cpw = g.DW / NWAVES;
   const int pairs_w = (cpw / 4) * g.MG;
-  hipLaunchKernelGGL(fwd_carry_kernel, dim3((unsigned)((npairs + pw - 1) / pw)), dim3(256), 0, st, a,
-                     seg_len, nseg, nsegp, pairs_per_tile, cpw, pairs_w);
+  const dim3 grid((unsigned)((npairs + pw - 1) / pw));
+  if (blk16)
+    hipLaunchKernelGGL(fwd_carry_kernel<CARRY_BLOCK_LONG>, grid, dim3(256), 0, st, a, seg_len, nseg, nsegp,
+                       pairs_per_tile, cpw, pairs_w);
+  else
+    hipLaunchKernelGGL(fwd_carry_kernel<CARRY_BLOCK>, grid, dim3(256), 0, st, a, seg_len, nseg, nsegp, pairs_per_tile,
+                       cpw, pairs_w);
   return hipGetLastError();
 }
 

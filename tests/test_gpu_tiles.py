@@ -66,3 +66,19 @@ def test_prompt_state_keeps_float32_bits(L, D, M, act):
     ref = O.state_init(x, *p)
     lim = O.state_init(np.abs(x), p[0], np.zeros_like(p[1]), *p[2:])[..., :1]  # sum of |lambda|^k |x|
     assert np.all(np.abs(st - ref) <= 17 * 2.0 ** -24 * lim + 1e-30)
+
+
+@pytest.mark.parametrize("B,L,D,M", [(8, 33000, 64, 9), (1, 33024, 24, 12), (1, 131328, 16, 16)])
+@pytest.mark.parametrize("act", ["f32", "bf16"])
+def test_forward_long_rows_wide_bank(B, L, D, M, act):
+    """Carry fold past 128 tiles a row: segments of 16 tiles (many rows, or more than
+    512 tiles) and of 4 tiles doubled."""
+    from paper_2607_05583_amd import ops
+    say(f"forward long rows B={B} L={L} D={D} M={M} {act}")
+    prob = _prob(L + M, B, L, D, M, act, with_h0=True)
+    y, h = ops.resonator_mix_fwd(dev_act(prob["x"], act), *params_dev(prob), h0=dev_f32(prob["h0"]), return_state=True)
+    rows = [0, B - 1] if B > 1 else [0]
+    x = act64(prob["x"], act)
+    yr, hr = O.mix_recurrence(x[rows], *params_np(prob), h0=prob["h0"][rows])
+    assert rel_err(host(y)[rows], yr) <= tol(act, act)
+    assert rel_err(host(h)[rows], hr) <= (1e-4 if act == "f32" else 2e-2)
