@@ -142,7 +142,7 @@ Geometry make_geom(res_dtype_t act, int64_t B, int64_t L, int64_t D, int64_t M) 
 // bytes are the header (status word first); the forward workspace must be zero
 // before its first use and each call leaves it ready for the next.
 struct StreamLayout {
-  size_t hdr, chainw, agg, ring, total;
+  size_t hdr, chainw, agg, total;
 };
 // The single-pass forward keeps per-chain counters in a fixed area of the
 // workspace (every call resets the counters it used), ahead of the tagged
@@ -162,8 +162,6 @@ StreamLayout make_stream_layout(const Geometry& g) {
   off += STREAM_CHAINW_BYTES;
   w.agg = off;
   off += align256(tiles * state);
-  w.ring = off;
-  off += align256((size_t)std::min(nchains, (size_t)STREAM_RING_CHAINS) * STREAM_RING * state);
   w.total = off;
   return w;
 }
@@ -179,6 +177,12 @@ WsLayout make_layout(int op, res_dtype_t act, const Geometry& g) {
     }
     off = STREAM_KEPT_BYTES;  // the status word and the single-pass forward's words
   }
+  if (op == RES_OP_STATE_INIT) {  // end states of the segments (complex float64): at most STREAM_GROUPS work-groups
+    w.agg = off;
+    off += align256((size_t)std::min<int64_t>(g.B * g.NB * g.P, STREAM_GROUPS) * g.DW * g.Mp * sizeof(double2));
+    w.total = off;
+    return w;
+  }
   const int nm = op == RES_OP_BWD ? bwd_mats(g.MG) : fwd_mats(g.MG);
   const size_t tiles_modes = (size_t)g.B * g.P * g.Dp * g.Mp;  // = tiles * DW * Mp
   w.tab = off;
@@ -187,14 +191,12 @@ WsLayout make_layout(int op, res_dtype_t act, const Geometry& g) {
   off += align256((size_t)g.Dp * g.Mp * sizeof(ModeScalars));
   w.carryc = off;
   off += align256((size_t)g.Dp * g.Mp * sizeof(ModeCarry));
-  if (op == RES_OP_FWD || op == RES_OP_STATE_INIT) {
+  if (op == RES_OP_FWD) {
     // per tile [DW * Mp] float4 records: half-tile aggregates, then entry states
     w.agg = off;
     off += align256(tiles_modes * sizeof(float4));
-    if (op == RES_OP_FWD) {
-      w.carry = off;
-      off += align256(tiles_modes * sizeof(float4));
-    }
+    w.carry = off;
+    off += align256(tiles_modes * sizeof(float4));
     w.alast = off;  // [B][Dp][Mp] state at t = L-1 from a zero start at the last tile
     off += align256((size_t)g.B * g.Dp * g.Mp * sizeof(float2));
   } else {
@@ -339,7 +341,6 @@ int mix_fwd_impl(const void* x, res_dtype_t x_dt, void* y, res_dtype_t y_dt, int
     a.hdr = (uint32_t*)(base + sl.hdr);
     a.chainw = (uint32_t*)(base + sl.chainw);
     a.agg = (uint64_t*)(base + sl.agg);
-    a.ring = B * g.NB <= STREAM_RING_CHAINS ? (uint64_t*)(base + sl.ring) : nullptr;
     const int grid = fwd_stream_grid(B * g.NB, g.P, ncu > 0 ? ncu : 256);
     a.G = grid / a.nchains;
     a.Sf = (int)(g.P / a.G);

@@ -7,8 +7,6 @@
 
 namespace res {
 
-enum { MODE_STATE = 0, MODE_APPLY = 1 };
-
 // Mixer epilogue: limits and the block of rows of the parameter sums
 constexpr int EPI_H_MAX = 32;   // heads
 constexpr int EPI_K_MAX = 16;   // local-path taps
@@ -33,14 +31,10 @@ inline size_t epi_workspace_bytes(int64_t B, int64_t L, int64_t H, int64_t dh, i
   return epi_bytes_of_rows(least > EPI_PARTS ? least : EPI_PARTS, H, dh, K);
 }
 
-// LDS tile buffers of the single-kernel forward work-group, by activation size
-// (bf16: 16 waves, 4 buffers; float32: 8 waves, 3 buffers)
-constexpr int seg_bufs(int elem_bytes) { return elem_bytes == 2 ? 4 : 3; }
-
-
+// Three-kernel forward (M > 8, or more chains than the single-pass one counts).
 struct FwdArgs {
   const void* x;
-  void* y;           // null for the prompt state
+  void* y;
   int64_t B, L;
   int D, M;
   int NB, Dp, Mp;
@@ -53,21 +47,9 @@ struct FwdArgs {
   const float* h0;   // [B][D][M][2] or null
   float* h_out;      // [B][D][M][2] or null: state at t = L-1
   void* agg;         // per tile [DW * Mp] float4: half-tile end states (A_0, A_1)
-  void* car;         // per tile [DW * Mp] float4: entry states of both halves (null: none)
+  void* car;         // per tile [DW * Mp] float4: entry states of both halves
   float2* alast;     // [B][Dp][Mp]: state at t = L-1 from a zero start at the last tile
 };
-
-// Single-pass forward (M <= 8): problem, parameters and the workspace regions.
-// A published segment state is a set of 64-bit words, each a float (low half)
-// and the call's tag, epoch + 1 (high half); hdr[1] holds the epoch.
-// Tile-to-tile chains (2 to 4 work-groups per chain) pass each tile's inclusive
-// end state to the next tile through a ring of STREAM_RING slots per chain; a
-// slot is written again only after the tile that read it has published its own
-// state, so any ring length is safe.  The ring is laid out for at most
-// STREAM_RING_CHAINS chains (more chains leave at most one work-group each on a
-// 256-CU device).
-constexpr int STREAM_RING = 4;
-constexpr int64_t STREAM_RING_CHAINS = 128;
 
 // First of a chain's four counter words (65536 chains in all).  The first 4096
 // chains have 256 bytes to themselves: the arrivals and decisions of a chain's
@@ -76,6 +58,10 @@ constexpr int64_t STREAM_RING_CHAINS = 128;
 __host__ __device__ inline size_t stream_chain_word(int chain) {
   return 64 * (size_t)(chain & 4095) + 4 * (size_t)(chain >> 12);
 }
+
+// Single-pass forward (M <= 8): problem, parameters and the workspace regions.
+// A published segment state is a set of 64-bit words, each a float (low half)
+// and the call's tag, epoch + 1 (high half); hdr[1] holds the epoch.
 struct StreamArgs {
   const void* x;
   void* y;
@@ -83,7 +69,7 @@ struct StreamArgs {
   int D, M;
   int NB;              // channel blocks of DW channels
   int nchains;         // B * NB
-  int G, Sf, Sr;   // work-groups of a chain; its tiles over them, quotient and remainder
+  int G, Sf, Sr;       // work-groups of a chain; its tiles over them, quotient and remainder
   int64_t P;           // tiles per chain
   int last_len;        // valid steps of a chain's last tile
   int fast_io;         // x and y 16-byte aligned and rows a multiple of 16 bytes
@@ -100,8 +86,6 @@ struct StreamArgs {
   uint64_t* agg;       // [nchains][G][DW / 4 waves][64] published state of each segment
                        // (float | tag << 32 per word); laid out for up to P segments.  The
                        // prompt state: [nchains][G][DW][modes] complex float64 end states
-  uint64_t* ring;       // [nchains][STREAM_RING][8 waves][64][DW / 32] I of recent tiles, or null:
-                        // no tile-to-tile chains
 };
 
 // Backward (M <= 16).  A chain is one batch row and one block of DW channels
