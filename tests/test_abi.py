@@ -87,6 +87,25 @@ def test_fwd_validation_codes():
     assert _fwd(ws=ctypes.c_void_p(0x7F0200000010), wsb=need) == L.RES_ERR_MISALIGNED
 
 
+def test_workspace_init_and_sizes_validation_codes():
+    lib = L.lib()
+    init = lambda dt=L.RES_F32, B=1, Ln=16, D=4, M=2, ws=None, wsb=0: lib.resonator_fwd_workspace_init(
+        dt, B, Ln, D, M, ws, wsb, None)
+    need = lambda *a: lib.resonator_workspace_bytes(*a)
+    n = need(L.RES_OP_FWD, L.RES_F32, 1, 16, 4, 2)
+    assert init(B=0) == L.RES_ERR_INVALID_ARG
+    assert init(Ln=0) == L.RES_ERR_INVALID_ARG
+    assert init(M=17) == L.RES_ERR_UNSUPPORTED
+    assert init(dt=5) == L.RES_ERR_INVALID_ARG
+    assert init() == L.RES_ERR_WORKSPACE
+    assert init(ws=FAKE, wsb=n - 1) == L.RES_ERR_WORKSPACE
+    assert init(ws=ctypes.c_void_p(0x7F0200000010), wsb=n) == L.RES_ERR_MISALIGNED
+    # prompt state: one record (complex float64 per channel of the block and mode of
+    # whole groups of 8) per tile, and per work-group where there are more tiles
+    assert need(L.RES_OP_STATE_INIT, L.RES_BF16, 2, 300, 65, 3) == 2 * 2 * 2 * 64 * 8 * 16
+    assert need(L.RES_OP_STATE_INIT, L.RES_F32, 4, 1 << 20, 64, 16) == 256 * 32 * 16 * 16
+
+
 def test_bwd_state_decode_validation_codes():
     lib = L.lib()
     rc = lib.resonator_mix_bwd(FAKE, FAKE2, L.RES_F32, FAKE, 1, 16, 4, 2, FAKE, FAKE, FAKE, FAKE,

@@ -278,7 +278,8 @@ def test_workspace_shared_by_both_forwards(noalloc):
 # a 256-byte header, then four 32-bit words per chain (next ticket, arrived
 # work-groups, tile order, finished work-groups).
 def _set_chain_word(ws, chain, j, value):
-    ws.view(torch.int32)[(256 + 16 * chain + 4 * j) // 4] = value
+    # after the 64-word header: 64 words to each of the first 4096 chains, later ones in between
+    ws.view(torch.int32)[64 + 64 * (chain % 4096) + 4 * (chain // 4096) + j] = value
 
 
 def _chain_g(nchains, P):

@@ -38,18 +38,20 @@ def _flat(o):
 
 
 def _both(monkeypatch, ops, call):
-    # memory the allocator hands out again: words of 1 (the tag of a first call) and of all ones
-    for fill in (0x01, 0xFF):
-        junk = torch.full((64 << 20,), fill, dtype=torch.uint8, device="cuda")
-        if fill == 1:
-            junk.view(torch.int64).fill_(1 << 32)
-        del junk
-        a = _flat(call())
+    # memory the allocator hands out again: words with the tag of a first call, and all ones
+    got = []
+    for word in (1 << 32, -1):
+        torch.cuda.empty_cache()
+        junk = torch.full((8 << 20,), word, dtype=torch.int64, device="cuda")
+        small = [torch.full((1 << 16,), word, dtype=torch.int64, device="cuda") for _ in range(16)]
+        del junk, small
+        got.append(_flat(call()))
     monkeypatch.setattr(ops, "_NATIVE", _Off())
     b = _flat(call())
-    assert len(a) == len(b)
-    for x, y in zip(a, b):
-        assert x.shape == y.shape and x.dtype == y.dtype and torch.equal(x, y)
+    for a in got:
+        assert len(a) == len(b)
+        for x, y in zip(a, b):
+            assert x.shape == y.shape and x.dtype == y.dtype and torch.equal(x, y)
 
 
 @pytest.mark.parametrize("B,L,D,M", [(1, 40, 8, 1), (2, 3000, 72, 8), (3, 1030, 65, 6), (2, 700, 64, 12)])
@@ -201,3 +203,53 @@ def test_decode_replay_under_capture(monkeypatch, ops, native):
         torch.cuda.synchronize()
         assert torch.equal(graph.y, w) and torch.equal(twice, w * 2) and torch.equal(live, ref)
         _ = (x * i).sum().item()  # eager work between the replays
+
+
+@pytest.mark.parametrize("dt,dh", [(torch.bfloat16, 32), (torch.float32, 16)])
+def test_block_graph_with_the_calls_own_workspace(ops, dt, dh):
+    """A captured block: its forward clears the words it uses of a workspace of its
+    own inside the capture.  Replays against eager calls, with eager work between."""
+    H, B, L, M, K = 4, 2, 1500, 8, 3
+    D = H * dh
+    say(f"block graph {dt} dh={dh}")
+    g = torch.Generator(device="cuda").manual_seed(dh + 1)
+    r = lambda *s: torch.randn(*s, device="cuda", generator=g)
+    W = [(r(H, dh, dh) / dh ** 0.5).to(dt) for _ in range(3)]
+    args = (*W, *_params(D, M, g), r(H, H), 0.5, r(D, K), r(D), H)
+    graph = ops.BlockForwardGraph(r(B, L, D).to(dt), *args)
+    for i in range(4):
+        x = r(B, L, D).to(dt)
+        want = ops.resonator_block_fwd(x, *args)
+        torch.cuda.synchronize()
+        got = graph.replay(x)
+        torch.cuda.synchronize()
+        assert torch.equal(got, want), i
+        _ = (x.float() * i).sum().item()
+
+
+@pytest.mark.parametrize("dt", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("keep", [False, True])
+def test_forward_past_4096_chains(ops, dt, keep):
+    """Chains 4096 .. use the second group of counter words; twice on one workspace.
+    Every row is the same problem, so the first row's float64 recurrence checks all."""
+    B, L, D, M = 9000, 40, 8, 5
+    say(f"forward chains={B} {dt} keep={keep}")
+    g = torch.Generator(device="cuda").manual_seed(8)
+    prm = _params(D, M, g)
+    row = torch.randn(1, L, D, device="cuda", generator=g).to(dt)
+    x, ws = row.expand(B, L, D).contiguous(), ops.forward_workspace(dt, B, L, D, M, "cuda") if keep else None
+    gam, om, amp, ph = (p.double().cpu() for p in prm)
+    lam = torch.exp(torch.complex(-gam, om))
+    h, want = torch.zeros(D, M, dtype=torch.complex128), []
+    for t in range(L):
+        h = lam * h + row[0, t].double().cpu()[:, None]
+        want.append((amp * torch.exp(1j * ph) * h).real.sum(-1))
+    want = torch.stack(want)
+    for _ in range(2):
+        y = ops.resonator_mix_fwd(x, *prm, ws=ws, out_dtype=torch.float32)
+        assert bool((y == y[:1]).all())
+        err = (y[0].double().cpu() - want).norm() / want.norm()
+        # float32 sums of some tens of terms; bf16 drives are exact, their tables 2^-17
+        assert err <= (1e-6 if dt == torch.float32 else 2.0 ** -15)
+        if keep:
+            assert ops.resonator_fwd_status(ws) == 0
