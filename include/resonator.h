@@ -499,9 +499,13 @@ int resonator_epilogue_proj_fwd(const void* y, const void* gate, const void* v, 
  *                    none may overlap the inputs or each other
  *   dCt [H][H], dw [D][K], ds [D], dlambda_c [1]  float32 device arrays, overwritten
  *                    (dw, ds may be NULL when K == 0)
- *   ws               workspace of resonator_epilogue_workspace_bytes(B, L, H, dh, K)
+ *   ws               workspace of resonator_epilogue_workspace_bytes(B, L, H, dh, K).
+ *                    A smaller one of n floats (n even, n >= B ceil(L / 64) (H H + H dh
+ *                    + H dh K)) and H H doubles is taken too; the rows of short inputs
+ *                    then go to fewer work-groups.
  * The parameter gradients are reduced in a fixed order (per block of rows, then
- * over blocks in float64), so they are bitwise reproducible.
+ * over blocks in float64), so calls with workspaces of one size are bitwise
+ * reproducible.
  */
 int resonator_epilogue_bwd(const void* y, const void* gate, const void* v, const void* dz, res_dtype_t act_dt,
                            void* dy, void* dgate, void* dv, int64_t B, int64_t L, int64_t H, int64_t dh, int64_t K,

@@ -215,3 +215,37 @@ def test_epilogue_bwd_many_blocks():
                          ids=lambda c: "B{}_L{}_H{}_dh{}_K{}_{}".format(*c))
 def test_epilogue_bwd_more_chunks_than_blocks(case):
     test_epilogue_bwd_parity(case)
+
+
+@pytest.mark.parametrize("case", [(2, 300, 8, 32, 4, "bf16"), (1, 40, 4, 16, 2, "f32"), (1, 100, 3, 7, 1, "f32")],
+                         ids=lambda c: "B{}_L{}_H{}_dh{}_K{}_{}".format(*c))
+def test_epilogue_bwd_smallest_workspace(case):
+    """The least workspace that a call takes: refused with a byte less, the gradients
+    within the bounds, the activations' bitwise those of the full size."""
+    from paper_2607_05583_amd import _lib as L
+    B, T, H, dh, K, act = case
+    say(f"epilogue bwd smallest workspace {case}")
+    p = W.epilogue_inputs(21, B, T, H, dh, K, act)
+    t = _dev_inputs(p, act)
+    full = ops.resonator_epilogue_bwd(t["y"], t["gate"], t["v"], t["dz"], t["Ct"], p["lambda_c"], t["w"], t["s"], H)
+    n = B * ((T + 63) // 64) * (H * H + H * dh + H * dh * K)
+    need = (n + n % 2) * 4 + H * H * 8
+    assert need < L.lib().resonator_epilogue_workspace_bytes(B, T, H, dh, K)
+    ws = torch.empty(need, dtype=torch.uint8, device="cuda")
+    outs = [torch.empty_like(g) for g in full]
+
+    def call(nb):
+        q = ops._ptr
+        return L.lib().resonator_epilogue_bwd(
+            q(t["y"]), q(t["gate"]), q(t["v"]), q(t["dz"]), ops._code(t["y"]), *map(q, outs[:3]), B, T, H, dh, K,
+            q(t["Ct"]), p["lambda_c"], q(t["w"]), q(t["s"]), *map(q, outs[3:]), q(ws), nb, ops._stream(ws.device))
+
+    assert call(need - 1) == L.RES_ERR_WORKSPACE
+    assert call(need) == L.RES_OK
+    torch.cuda.synchronize()
+    first = [o.clone() for o in outs]
+    assert call(need) == L.RES_OK
+    assert all(torch.equal(a, b) for a, b in zip(first, outs))
+    assert all(torch.equal(a, b) for a, b in zip(full[:3], outs[:3]))
+    for a, b in zip(full[3:], outs[3:]):  # float32 sums of the same terms in other groups
+        assert float((a.double() - b.double()).norm()) <= _bounds(act)[1] * float(a.double().norm())
