@@ -731,6 +731,7 @@ __global__ __launch_bounds__(BGeo<TX>::NT, 1) void bwd_apply_kernel(BwdArgs a) {
       Qc[g] = Q;
       Rc[g] = Rr;
       wave_lds_order();
+      if (sizeof(TX) == 2 && g == 0) mfma_depth_change(dxa);  // T dy is 32 deep, U H 16
 #pragma unroll
       for (int c = 0; c < 4; ++c) {
         const f4 h = *reinterpret_cast<const f4*>(&hw[c * BH_K + ln * BH_P + 4 * lq]);

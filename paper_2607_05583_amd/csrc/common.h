@@ -66,6 +66,15 @@ template <> __device__ __forceinline__ bf16_t from_f32<bf16_t>(float v) {
 // ---------------------------------------------------------------------------
 typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
 
+// A 16-deep bf16 product that accumulates onto a 32-deep one, or the other way
+// round, reads half of its rows stale unless five wait states lie between the two
+// (measured on gfx950, in both orders: wrong up to four, right from five; products of
+// one depth and float32 ones need none).  hipcc of ROCm 7.2 inserts none for such
+// pairs, so the code that chains them does, on the four accumulators of a group.
+__device__ __forceinline__ void mfma_depth_change(f4 (&c)[4]) {
+  asm volatile("s_nop 4" : "+v"(c[0]), "+v"(c[1]), "+v"(c[2]), "+v"(c[3]));
+}
+
 __device__ __forceinline__ f4 mma_f32(const f4& a, const f4& b, f4 c) {
   c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[0], b[0], c, 0, 0, 0);
   c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[1], b[1], c, 0, 0, 0);

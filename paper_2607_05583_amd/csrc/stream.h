@@ -206,8 +206,7 @@ template <> struct FPath<bf16_t> {
   // y = T x + U H as three 32-deep products: the contraction index is shared out
   // so that lane (n, q) holds steps 4q .. 4q+3 of x and then components
   // 4q .. 4q+3 of H; [Th | Uh] and [Tl | Ul] meet [x | Hh], and [Th | Uh] meets
-  // [0 | Hl].  (Not a 16-deep product for the last: accumulating a 16-deep
-  // product onto a 32-deep one right behind it gave stale sums on gfx950.)
+  // [0 | Hl].  (Not a 16-deep product for the last: see mfma_depth_change.)
   struct OOp {
     bf8 hi, lo;
   };
