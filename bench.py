@@ -10,7 +10,7 @@ exceeds the 256 MB Infinity Cache.  The JSON line also carries
 
   decode    steps/s of the decode workload (B=64, D=256, M=8, state from a
             1024-step prompt), eager (one C call per step from Python) and
-            replayed from a captured HIP graph of the same calls;
+            as one launch of 512 known steps, replayed from a captured HIP graph;
   train     one forward + backward of a training layer (B=8, L=8192, D=256, M=8,
             bf16), as time per layer;
   roofline  the dominant kernel (the single-pass streaming forward kernel) against the HBM
@@ -134,7 +134,7 @@ def main():
                          "(decode); prints one JSON line and skips everything else")
     args = ap.parse_args()
     if args.gpus != 1:
-        print(f"bench.py measures one GPU only: this build runs the operator on a single "
+        print(f"bench.py measures one GPU only: the library runs the operator on a single "
               f"MI355X (got --gpus {args.gpus}); sharding across GPUs is not part of it.",
               file=sys.stderr)
         sys.exit(2)
@@ -413,7 +413,7 @@ def main():
     d1.record(stream)
     torch.cuda.synchronize()
     dec_eager_us = d0.elapsed_time(d1) * 1e3 / nsteps
-    # graph replay of the same calls (kernel launches only; no allocation, no memset)
+    # the same steps as one launch of G steps, replayed from a captured graph
     G = min(512, int(xdec.shape[0]))
     dgraph = ops.DecodeGraph(*dprm, state, G, x_dtype=torch.bfloat16)
     dgraph.x.copy_(xdec[:G])
@@ -428,7 +428,8 @@ def main():
     d1.record(stream)
     torch.cuda.synchronize()
     dec_graph_us = d0.elapsed_time(d1) * 1e3 / (reps * G)
-    # launch floor of a replayed graph: G launches of a one-element kernel
+    # for comparison, the least that one launch a step takes in a graph: G launches of
+    # a one-element kernel
     tiny = torch.zeros(1, dtype=torch.float32, device=dev)
     fgraph = torch.cuda.CUDAGraph()
     fcap = torch.cuda.Stream(dev)
@@ -446,9 +447,9 @@ def main():
     torch.cuda.synchronize()
     floor_us = d0.elapsed_time(d1) * 1e3 / (reps * G)
     del fgraph
-    dec_bytes = Bd * Dd * (Md * 16 + 2 + 2)
+    dec_graph_bytes = Bd * Dd * (Md * 16 / G + 2 + 2)  # a step of a block: the state once per G steps
     log(f"decode: eager {dec_eager_us:.2f} us/step, graph {dec_graph_us:.2f} us/step "
-        f"(replayed one-element launches: {floor_us:.2f} us each)")
+        f"(one launch of {G} steps; a graph of one-element launches: {floor_us:.2f} us each)")
     # several steps per launch, for drives known in advance: 8 drafted tokens to
     # verify per launch, and a long run of known drives in one launch
     xbn = xdec.permute(1, 0, 2).contiguous()  # [B, N, D]
@@ -687,7 +688,7 @@ def main():
                    "steps_per_s_eager": 1e6 / dec_eager_us, "us_per_step_eager": dec_eager_us,
                    "steps_per_s_graph": 1e6 / dec_graph_us, "us_per_step_graph": dec_graph_us,
                    "graph_launch_floor_us": floor_us, "graph_over_floor": dec_graph_us / floor_us,
-                   "alg_GBs_graph": dec_bytes / (dec_graph_us * 1e-6) / 1e9},
+                   "graph_steps_per_launch": G, "alg_GBs_graph": dec_graph_bytes / (dec_graph_us * 1e-6) / 1e9},
         "train_layer": {"workload": "B8 L8192 D256 M8 bf16 (one of the 6 layers)",
                         "fwd_us": tr_fwd_us, "bwd_us": tr_bwd_us,
                         "bwd_alg_GBs": 8 * 8192 * 256 * 6 / (tr_bwd_us * 1e-6) / 1e9},

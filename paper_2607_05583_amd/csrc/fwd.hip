@@ -740,7 +740,10 @@ struct StreamGeo {
   // registers each) | 8 (float).  More waves, not more channels per wave: a tile
   // step is a chain of LDS and matrix latencies that the other waves of the SIMD
   // fill (bf16 with 8 waves of 8 channels: 61 against 53 thousand cycles for the
-  // output pass at B4 L32K).
+  // output pass at B4 L32K).  The price: the bf16 instances spill 8 to 16 registers
+  // (36 to 68 bytes of scratch a lane).  With 16-byte pieces the spills lie outside the
+  // tile loops, and the reload before phase B waits for the loads of tiles 1 and 2
+  // where phase A is skipped.
   static constexpr int NW = DW / 4;
   static constexpr int NT = 64 * NW;
   static constexpr int GPL = (TILE_T / 8) / NW;    // row groups per wave and tile
