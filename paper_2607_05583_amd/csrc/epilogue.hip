@@ -799,15 +799,20 @@ static hipError_t tile_bwd(const void* y, const void* gate, const void* v, const
                            void* dv, int64_t B, int64_t L, int H, int dh, int K, const float* Ct, float lambda_c,
                            const float* w, const float* s, float* part, int64_t cap, int64_t* nparts,
                            hipStream_t st) {
+  // by registers and the most LDS a chunk takes: a constant of the instance, asked for
+  // once (the query takes 2 us of host time)
+  static const int per = [] {
+    int n = 0;
+    const hipError_t e =
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, epi_bwd_tile_kernel<T, CPT, HM>, 256, EPI_TILE_LDS_MAX);
+    return e == hipSuccess && n > 0 ? n : 1;
+  }();
   int R = epi_tile_rows(true, H * dh, H, K, CPT, sizeof(T));
-  int dev = 0, ncu = 0, per = 0;
+  int dev = 0, ncu = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e == hipSuccess) e = hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
-  if (e == hipSuccess)
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, epi_bwd_tile_kernel<T, CPT, HM>, 256,
-                                                     epi_tile_lds(true, H * dh, H, K, CPT, sizeof(T), R));
   if (e != hipSuccess) return e;
-  const int64_t run = (int64_t)(per < 1 ? 1 : per) * (ncu < 1 ? 256 : ncu);
+  const int64_t run = (int64_t)per * (ncu < 1 ? 256 : ncu);
   const int RP = tile_geo(H * dh, CPT).RP;
   while (R - RP >= RP && B * ((L + R - 1) / R) < run) R -= RP;
   const int64_t nch = B * ((L + R - 1) / R);
