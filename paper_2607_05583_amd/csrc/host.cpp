@@ -15,6 +15,7 @@
 
 #include <ATen/Functions.h>
 #include <c10/core/DeviceGuard.h>
+#include <c10/hip/HIPFunctions.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/Dtype.h>
 #include <torch/csrc/Exceptions.h>
@@ -51,10 +52,13 @@ float* fpm(const Tensor& t) { return static_cast<float*>(t.data_ptr()); }
 // scope (a device's default stream is the null stream, which means the current
 // device) and its current stream.
 struct OnDevice {
-  c10::DeviceGuard guard;
+  c10::OptionalDeviceGuard guard;
   void* stream;
-  explicit OnDevice(const Tensor& t)
-      : guard(t.device()), stream(c10::hip::getCurrentHIPStream(t.device().index()).stream()) {}
+  explicit OnDevice(const Tensor& t) : stream(c10::hip::getCurrentHIPStream(t.device().index()).stream()) {
+    // (the count is kept by c10: a process with one GPU asks nothing, 0.15 us a call)
+    if (c10::hip::device_count() > 1 && t.device().index() != c10::hip::current_device())
+      guard.reset_device(t.device());
+  }
 };
 Tensor empty(at::IntArrayRef s, const Tensor& like, at::ScalarType dt) {
   return at::empty(s, at::TensorOptions().device(like.device()).dtype(dt));
